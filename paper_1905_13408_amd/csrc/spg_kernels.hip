@@ -1303,6 +1303,7 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
   __syncthreads();
   compute_p(1, 0, 0, rv, true);
   fetch_plane(z0 + 1, rown, rhalo, rv);
+  __syncthreads();  // the first step rewrites the plane z0 - 1 that p(z0) was formed from
   int cur = 0, ycur = 1;
 
   for (int z = z0; z < z1; ++z) {
