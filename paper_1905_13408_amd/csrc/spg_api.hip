@@ -839,6 +839,23 @@ void twiddle_table(int n, std::vector<float2>& tab) {
   }
 }
 
+// The tables of nx/2, nx, ny and nz points at the workspace offsets offs (relative to the
+// first).  An axis of the same length is copied, and the nx/2 table is every second entry of
+// the nx table (the same angle: only a power of two apart).
+void fsc_tables(int nx, int ny, int nz, char* dst, const size_t offs[4]) {
+  std::vector<float2> tx, ty, tz;
+  twiddle_table(nx, tx);
+  if (ny == nx) ty = tx;
+  else twiddle_table(ny, ty);
+  if (nz == nx) tz = tx;
+  else if (nz == ny) tz = ty;
+  else twiddle_table(nz, tz);
+  std::vector<float2> tm(nx / 2);
+  for (int m = 0; m < nx / 2; ++m) tm[m] = tx[2 * m];
+  const std::vector<float2>* src[4] = {&tm, &tx, &ty, &tz};
+  for (int t = 0; t < 4; ++t) std::memcpy(dst + (offs[t] - offs[0]), src[t]->data(), src[t]->size() * sizeof(float2));
+}
+
 // Both maps to the packed half spectrum (x, y, z transforms), the shell sums and the ratio
 // of eq 30.  ws holds the spectra, partials and output at the offsets of lay; tw[4] are the
 // twiddle tables of nx/2, nx, ny and nz points.  Synchronises the stream.
@@ -955,18 +972,18 @@ spg_status spg_fsc(int32_t nx, int32_t ny, int32_t nz, const float* d_map1, cons
   if (bytes < lay.total) return SPG_E_NOMEM;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   char* ws = reinterpret_cast<char*>(d_workspace);
-  const int lens[4] = {nx / 2, nx, ny, nz};
+  // the four tables as they lie in the workspace, in one copy; fsc_run synchronises, and host
+  // memory outlives the stream's use of it on the way out of a failed launch too
   const size_t offs[4] = {lay.tw_m, lay.tw_n, lay.tw_y, lay.tw_z};
-  std::vector<float2> tab;
+  std::vector<char> tabs(lay.part - lay.tw_m);
+  fsc_tables(nx, ny, nz, tabs.data(), offs);
   const float2* tw[4];
-  for (int t = 0; t < 4; ++t) {
-    twiddle_table(lens[t], tab);
-    if (hipMemcpyAsync(ws + offs[t], tab.data(), lens[t] * sizeof(float2), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-      return SPG_E_DEVICE;
-    tw[t] = reinterpret_cast<const float2*>(ws + offs[t]);
-  }
-  return fsc_run(nx, ny, nz, d_map1, d_map2, nshells, ws, lay, tw, st, h_fsc);
+  for (int t = 0; t < 4; ++t) tw[t] = reinterpret_cast<const float2*>(ws + offs[t]);
+  if (hipMemcpyAsync(ws + lay.tw_m, tabs.data(), tabs.size(), hipMemcpyHostToDevice, st) != hipSuccess)
+    return SPG_E_DEVICE;
+  const spg_status s = fsc_run(nx, ny, nz, d_map1, d_map2, nshells, ws, lay, tw, st, h_fsc);
+  if (s) (void)hipStreamSynchronize(st);
+  return s;
 }
 
 }  // extern "C"
