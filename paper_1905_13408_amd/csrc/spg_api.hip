@@ -1550,7 +1550,7 @@ spg_status spg_backproject(int32_t nx, int32_t ny, int32_t nz, int32_t n_img, in
   if (bytes < need) return SPG_E_NOMEM;
   Dims d{nx, ny, nz, nx / 2, (long long)nx * ny * nz};
   if (launch_backproject(d, n_img, m, reinterpret_cast<const float2*>(d_images), d_rot, d_ctf, d_weight, h,
-                         d_workspace, d_w_out, reinterpret_cast<float2*>(d_b_out),
+                         d_workspace, need, d_w_out, reinterpret_cast<float2*>(d_b_out),
                          reinterpret_cast<hipStream_t>(hip_stream)) != hipSuccess)
     return SPG_E_DEVICE;
   return SPG_OK;

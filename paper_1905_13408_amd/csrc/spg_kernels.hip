@@ -2563,31 +2563,59 @@ __global__ void __launch_bounds__(256) k_expand_bbar(Dims d, const float2* __res
 // the int64 range.  The maxima are exact whatever
 // the order of their atomics.
 
+// An image whose matrix is a rotation to 1e-5: its first two columns are orthonormal, so
+// that they are also the rows of the map back from a location to (u, v).
+constexpr double BP_ORTHO_TOL = 1e-5;
+__device__ __forceinline__ bool bp_rotation(const double* __restrict__ R) {
+  const double a = R[0] * R[0] + R[3] * R[3] + R[6] * R[6];
+  const double b = R[1] * R[1] + R[4] * R[4] + R[7] * R[7];
+  const double c = R[0] * R[1] + R[3] * R[4] + R[6] * R[7];
+  return fabs(a - 1.0) <= BP_ORTHO_TOL && fabs(b - 1.0) <= BP_ORTHO_TOL && fabs(c) <= BP_ORTHO_TOL;  // NaN: false
+}
+
 // The largest |p ctf Re X|, |p ctf Im X| and p ctf^2 over all pixels, kept as the bit
-// patterns of non-negative doubles (which order like their values) in mx[0..3).
-__global__ void __launch_bounds__(256) k_bp_max(int n_img, int m, const float2* __restrict__ images,
-                                                const float* __restrict__ ctf, const float* __restrict__ weights,
-                                                unsigned long long* __restrict__ mx) {
-  __shared__ double s_red[4];
+// patterns of non-negative doubles (which order like their values) in mx[0..3); with
+// other != nullptr, *other becomes 1 where any image's matrix is not a rotation.  A block
+// takes one contiguous run of pixels, image by image.  At most one block per CU, and an
+// atomic only where it would change the word: the atomics of all blocks queue up on one
+// cache line, about 13 ns each (47 us with three from each of 1024 blocks for 200 images of
+// 128^2, 20 us now).
+constexpr int BP_MAX_NT = 1024;
+__global__ void __launch_bounds__(BP_MAX_NT) k_bp_max(int n_img, int m, const float2* __restrict__ images,
+                                                const double* __restrict__ rots, const float* __restrict__ ctf,
+                                                const float* __restrict__ weights, unsigned long long* __restrict__ mx,
+                                                unsigned long long* __restrict__ other) {
+  __shared__ double s_red[BP_MAX_NT / 64];
   const long long npix = (long long)m * m;
   const long long total = npix * n_img;
+  const long long per = (total + gridDim.x - 1) / gridDim.x;
+  const long long c0 = per * blockIdx.x, c1 = min(total, c0 + per);
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-  for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total; t += (long long)gridDim.x * blockDim.x) {
-    const float2 X = images[t];
-    const double cf = ctf ? (double)ctf[t] : 1.0;
-    const double p = weights ? (double)weights[t / npix] : 1.0;
-    a0 = fmax(a0, fabs(p * cf * X.x));
-    a1 = fmax(a1, fabs(p * cf * X.y));
-    a2 = fmax(a2, fabs(p * cf * cf));
+  for (long long i = c0 / npix; i < n_img && i * npix < c1; ++i) {
+    const double p = weights ? (double)weights[i] : 1.0;
+    const long long e = min(c1, (i + 1) * npix);
+    for (long long t = max(c0, i * npix) + threadIdx.x; t < e; t += BP_MAX_NT) {
+      const float2 X = images[t];
+      const double pc = p * (ctf ? (double)ctf[t] : 1.0);
+      a0 = fmax(a0, fabs(pc * X.x));
+      a1 = fmax(a1, fabs(pc * X.y));
+      a2 = fmax(a2, fabs(ctf ? pc * ctf[t] : pc));
+    }
   }
   a0 = block_reduce<RED_OP_MAX>(a0, s_red);
   a1 = block_reduce<RED_OP_MAX>(a1, s_red);
   a2 = block_reduce<RED_OP_MAX>(a2, s_red);
   if (threadIdx.x == 0) {
-    atomicMax(&mx[0], (unsigned long long)__double_as_longlong(a0));
-    atomicMax(&mx[1], (unsigned long long)__double_as_longlong(a1));
-    atomicMax(&mx[2], (unsigned long long)__double_as_longlong(a2));
+    const double v[3] = {a0, a1, a2};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {  // the word only grows: a value no larger than it has nothing to add
+      const unsigned long long q = (unsigned long long)__double_as_longlong(v[c]);
+      if (q > __hip_atomic_load(&mx[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&mx[c], q);
+    }
   }
+  if (other)
+    for (long long i = blockIdx.x * (long long)BP_MAX_NT + threadIdx.x; i < n_img; i += gridDim.x * (long long)BP_MAX_NT)
+      if (!bp_rotation(rots + 9 * i)) atomicMax(other, 1ull);
 }
 
 // 2^s for the component whose largest term magnitude has the bits `mx`: the power of two
@@ -2606,12 +2634,16 @@ __device__ __forceinline__ double bp_scale(unsigned long long mx, long long tota
 // K = exp(-|c - n|^2 / h), accumulating num += p K ctf X and N += p K ctf^2 (eq 28) as
 // fixed-point terms.  The coordinate products are rounded separately (no fused
 // multiply-add) so that the rounding of c, which decides the neighbourhood, is the
-// reference's.
+// reference's.  Atomics to memory: the path of calls and of images that k_bp_tiles does not
+// take.  With other != nullptr only the images whose matrix is not a rotation (*other == 0:
+// none, the block ends at once).
 __global__ void __launch_bounds__(256) k_backproject(Dims d, int n_img, int m, const float2* __restrict__ images,
                                                      const double* __restrict__ rots, const float* __restrict__ ctf,
                                                      const float* __restrict__ weights, double h,
                                                      unsigned long long* __restrict__ acc,
-                                                     const unsigned long long* __restrict__ mx) {
+                                                     const unsigned long long* __restrict__ mx,
+                                                     const unsigned long long* __restrict__ other) {
+  if (other && *other == 0ull) return;
   const long long npix = (long long)m * m;
   const long long total = npix * n_img;
   const double s0 = bp_scale(mx[0], total), s1 = bp_scale(mx[1], total), s2 = bp_scale(mx[2], total);
@@ -2622,6 +2654,7 @@ __global__ void __launch_bounds__(256) k_backproject(Dims d, int n_img, int m, c
     const double u = ui < (m + 1) / 2 ? ui : ui - m;
     const double v = vi < (m + 1) / 2 ? vi : vi - m;
     const double* R = rots + 9LL * i;
+    if (other && bp_rotation(R)) continue;
     double c[3];
     long long base[3];
 #pragma unroll
@@ -2664,9 +2697,300 @@ __global__ void k_backproject_final(long long n, long long total, const unsigned
   }
 }
 
-__global__ void k_fill_f64(double* __restrict__ dst, long long n) {
+// dst = 0; with `only` given, only where *only is set.
+__global__ void k_fill_f64(double* __restrict__ dst, long long n, const unsigned long long* __restrict__ only) {
+  if (only && *only == 0ull) return;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
     dst[i] = 0.0;
+}
+
+// The same sums by volume tiles.  A block owns T^3 grid points and keeps their three int64
+// sums in LDS, so that the 81 additions of a pixel are LDS atomics; it writes w and b of its
+// points itself, and no sum goes to memory.  (Atomics to memory pass about 24 G/s over the
+// whole card: 10.95 ms for 200 images of 128^2 into 128^3; 0.32 ms here.)
+// Which pixels reach the tile:  every periodic copy of the tile within reach of the images
+// (|c| <= m / sqrt 2) is a box of half width (T - 1) / 2 + 3/2 around its centre; an image
+// reaches it if the box meets the image's plane, and then in the rectangle of (u, v) that
+// the box spans along the two columns of R (orthonormal, so they map back; the tolerance is
+// added).  One thread tests one (copy, image) pair and lists the hits; the waves walk the
+// rectangles of the hits and queue the pixels in the box (fp32, with a margin: a pixel
+// queued for nothing adds nothing); then the block spreads the queue, 64 pixels per wave,
+// with the exact coordinates, so that hardly a lane idles.  K costs four exponentials per
+// pixel instead of 27.  Integer sums: the same bits whatever the order of images, tiles or
+// waves.  Bound by fp64 arithmetic; a pixel is evaluated by (1 + 2 / T)^3 tiles on average,
+// and the few tiles around k = 0, which every image crosses, run first and at a higher wave
+// priority than the blocks they share a CU with, or they would end last by far.
+constexpr int BP_NT = 512;       // threads per block (256 and 1024: 20% slower at 128^3)
+constexpr int BP_COPIES = 64;    // periodic copies of a tile: at most 4 per axis for m <= 2 n
+constexpr int BP_QUEUE = 2048;   // queued pixels
+template <int T>
+struct BpTile {
+  // LDS pitches of the sums: points of a plane of any orientation spread over the banks
+  static constexpr int YP = T + 1, ZP = T * (T + 1) + 3;
+  static constexpr int WORDS = T * ZP;
+};
+
+// K = exp(-(f - k)^2 / h) for k = -1, 0, 1 of one axis up to the factor exp(-f^2 / h), which
+// the caller takes once for the three axes: exp(-1/h) exp(+-2 f / h) and 1.
+__device__ __forceinline__ void bp_side(double f, double inv_h, double e1, double K[3]) {
+  const double g = exp(2.0 * f * inv_h);
+  double r = __builtin_amdgcn_rcp(g);
+  r = __fma_rn(r, __fma_rn(-g, r, 1.0), r);
+  r = __fma_rn(r, __fma_rn(-g, r, 1.0), r);
+  K[0] = e1 * r;
+  K[1] = 1.0;
+  K[2] = e1 * g;
+}
+
+template <int T>
+__global__ void __launch_bounds__(BP_NT) k_bp_tiles(Dims d, int n_img, int m, const float2* __restrict__ images,
+                                                    const double* __restrict__ rots, const float* __restrict__ ctf,
+                                                    const float* __restrict__ weights, double inv_h,
+                                                    const unsigned long long* __restrict__ acc,
+                                                    const unsigned long long* __restrict__ mx,
+                                                    const unsigned long long* __restrict__ other,
+                                                    float* __restrict__ w, float2* __restrict__ b) {
+  constexpr int YP = BpTile<T>::YP, ZP = BpTile<T>::ZP, WORDS = BpTile<T>::WORDS;
+  constexpr int NWAVE = BP_NT / 64;
+  __shared__ unsigned long long s_acc[3][WORDS];
+  __shared__ int4 s_copy[BP_COPIES];      // grid coordinates of the copies' first points
+  __shared__ int4 s_item[BP_NT];          // image << 6 | copy, first u, first v, extents
+  __shared__ uint2 s_queue[BP_QUEUE];     // image << 6 | copy, (u, v)
+  __shared__ int s_n[4];                  // copies, items, queued pixels, waves with items left
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // tile of this block: axis order 0, last, 1, last - 1, ... puts the tiles around k = 0
+  // first; the order along x is rotated from row to row, or each of the 8 XCDs, which take
+  // blocks in turn, would get the same few x all over and two of them most of the work
+  const int n[3] = {d.nx, d.ny, d.nz};
+  int t0[3], e[3], far = 0;
+  {
+    int q3[3];
+    int r = blockIdx.x;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int nt = (n[a] + T - 1) / T;
+      q3[a] = r % nt;
+      r /= nt;
+    }
+    q3[0] = (q3[0] + q3[1] + q3[2]) % ((n[0] + T - 1) / T);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int nt = (n[a] + T - 1) / T, q = q3[a];
+      t0[a] = T * (q & 1 ? nt - 1 - (q >> 1) : q >> 1);
+      e[a] = min(T, n[a] - t0[a]);
+      far = max(far, q >> 1);
+    }
+  }
+  if (far == 0) __builtin_amdgcn_s_setprio(3);
+  else if (far == 1) __builtin_amdgcn_s_setprio(2);
+  else if (far == 2) __builtin_amdgcn_s_setprio(1);
+  for (int i = tid; i < 3 * WORDS; i += BP_NT) (&s_acc[0][0])[i] = 0ull;
+  const double marg = 1e-3 + BP_ORTHO_TOL * m;
+  const double reach = 0.70711 * m + 1.0;
+  double hw[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) hw[a] = 0.5 * (e[a] - 1) + 1.5;
+  if (tid == 0) {
+    int lo[3], hi[3], nc = 0;
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = (int)ceil((-reach - 1.5 - (t0[a] + e[a] - 1)) / n[a]);
+      hi[a] = (int)floor((reach + 1.5 - t0[a]) / n[a]);
+    }
+    for (int jz = lo[2]; jz <= hi[2]; ++jz)
+      for (int jy = lo[1]; jy <= hi[1]; ++jy)
+        for (int jx = lo[0]; jx <= hi[0]; ++jx) {
+          const int g[3] = {t0[0] + jx * n[0], t0[1] + jy * n[1], t0[2] + jz * n[2]};
+          double r2 = 0.0;
+          for (int a = 0; a < 3; ++a) {
+            const double q = fmax(0.0, fabs(g[a] + 0.5 * (e[a] - 1)) - hw[a]);
+            r2 += q * q;
+          }
+          if (r2 <= reach * reach && nc < BP_COPIES) s_copy[nc++] = make_int4(g[0], g[1], g[2], 0);
+        }
+    s_n[0] = nc;
+  }
+  const long long npix = (long long)m * m;
+  const long long total = npix * n_img;
+  const double s0 = bp_scale(mx[0], total), s1 = bp_scale(mx[1], total), s2 = bp_scale(mx[2], total);
+  // Terms below 2^50 in magnitude round to integers in the low mantissa bits of 1.5 2^52 + x
+  // (the exact product, one fused operation); the scale leaves 27 * pixels in the way of 2^62,
+  // so that holds from 152 pixels on unless a magnitude was not finite.
+  // K from four exponentials needs exp(+-1/h) well inside the range.
+  bool quick = total >= 152 && inv_h <= 100.0;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) quick = quick && __longlong_as_double((long long)mx[c]) * (double)total * 27.0 < 1e300;
+  const double e1 = exp(-inv_h);
+  const int ulo = -(m / 2), uhi = (m - 1) / 2;
+  __syncthreads();
+  const unsigned pairs = (unsigned)s_n[0] * (unsigned)n_img;
+
+  // spread one queued pixel (fast: both conditions above hold, as they do but for odd calls)
+  auto spread = [&](uint2 en, auto fast_) {
+    constexpr bool fast = decltype(fast_)::value;
+    const int img = (int)(en.x >> 6);
+    const int4 cp = s_copy[en.x & 63u];
+    const int u = (int)(short)(en.y & 0xffffu), v = (int)(short)(en.y >> 16);
+    const double* __restrict__ R = rots + 9LL * img;
+    const long long t = npix * img + (long long)(v < 0 ? v + m : v) * m + (u < 0 ? u + m : u);
+    const float2 X = images[t];
+    const double cf = ctf ? (double)ctf[t] : 1.0;
+    const double p = weights ? (double)weights[img] : 1.0;
+    double K[3][3], f[3];
+    int l[3];
+    const int g0[3] = {cp.x, cp.y, cp.z};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double c = __dadd_rn(__dmul_rn(R[3 * a + 0], (double)u), __dmul_rn(R[3 * a + 1], (double)v));
+      const double base = floor(__dadd_rn(c, 0.5));
+      l[a] = (int)base - g0[a];
+      f[a] = c - base;
+    }
+    double k0 = 1.0;
+    if constexpr (fast) {
+      k0 = exp(-(f[0] * f[0] + f[1] * f[1] + f[2] * f[2]) * inv_h);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) bp_side(f[a], inv_h, e1, K[a]);
+    } else {
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) K[a][k] = exp(-((f[a] - (k - 1)) * (f[a] - (k - 1))) * inv_h);
+    }
+    // a term that is not a number counts as 0, as its conversion to an integer gives
+    auto num = [](double x) { return x == x ? x : 0.0; };
+    const double wr = num(p * cf * X.x * s0), wi = num(p * cf * X.y * s1), ww = num(p * cf * cf * s2);
+    const int o = l[2] * ZP + l[1] * YP + l[0];
+    auto add = [&](int c, int at, double x, double wt) {
+      unsigned long long q;
+      if constexpr (fast)
+        q = (unsigned long long)__double_as_longlong(__fma_rn(x, wt, 6755399441055744.0)) - 0x4338000000000000ull;
+      else q = (unsigned long long)__double2ll_rn(x * wt);
+      atomicAdd(&s_acc[c][at], q);
+    };
+    const bool okx[3] = {(unsigned)(l[0] - 1) < (unsigned)e[0], (unsigned)l[0] < (unsigned)e[0],
+                         (unsigned)(l[0] + 1) < (unsigned)e[0]};
+#pragma unroll
+    for (int z = 0; z < 3; ++z) {
+      if ((unsigned)(l[2] + z - 1) >= (unsigned)e[2]) continue;
+      const double kz = k0 * K[2][z];
+#pragma unroll
+      for (int y = 0; y < 3; ++y) {
+        if ((unsigned)(l[1] + y - 1) >= (unsigned)e[1]) continue;
+        const double kzy = kz * K[1][y];
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+          if (!okx[x]) continue;
+          const double k = kzy * K[0][x];
+          const int at = o + (z - 1) * ZP + (y - 1) * YP + (x - 1);
+          add(0, at, k, wr);
+          add(1, at, k, wi);
+          add(2, at, k, ww);
+        }
+      }
+    }
+  };
+
+  for (unsigned base = 0; base < pairs; base += BP_NT) {
+    if (tid < 3) s_n[1 + tid] = 0;
+    __syncthreads();
+    // ---- one (copy, image) pair per thread
+    const unsigned pr = base + tid;
+    if (pr < pairs) {
+      const int ci = (int)(pr / (unsigned)n_img), img = (int)(pr - (unsigned)ci * (unsigned)n_img);
+      const double* __restrict__ R = rots + 9LL * img;
+      if (bp_rotation(R)) {
+        const int4 cp = s_copy[ci];
+        const double q[3] = {cp.x + 0.5 * (e[0] - 1), cp.y + 0.5 * (e[1] - 1), cp.z + 0.5 * (e[2] - 1)};
+        const double nv[3] = {R[3] * R[7] - R[6] * R[4], R[6] * R[1] - R[0] * R[7], R[0] * R[4] - R[3] * R[1]};
+        double dn = 0.0, wn = 0.0, du = 0.0, wu = 0.0, dv = 0.0, wv = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          dn += nv[a] * q[a];
+          wn += fabs(nv[a]) * hw[a];
+          du += R[3 * a] * q[a];
+          wu += fabs(R[3 * a]) * hw[a];
+          dv += R[3 * a + 1] * q[a];
+          wv += fabs(R[3 * a + 1]) * hw[a];
+        }
+        if (fabs(dn) <= wn + marg) {
+          const int ua = max(ulo, (int)ceil(du - wu - marg)), ub = min(uhi, (int)floor(du + wu + marg));
+          const int va = max(ulo, (int)ceil(dv - wv - marg)), vb = min(uhi, (int)floor(dv + wv + marg));
+          if (ua <= ub && va <= vb) {
+            const int k = atomicAdd(&s_n[1], 1);
+            s_item[k] = make_int4((img << 6) | ci, ua, va, (ub - ua + 1) | ((vb - va + 1) << 16));
+          }
+        }
+      }
+    }
+    __syncthreads();
+    const int items = s_n[1];
+    int it = wave, c0 = 0;  // this wave's place in the list of hits
+    for (;;) {
+      // ---- queue the pixels of the hits, until every wave is done or the queue is nearly full
+      while (it < items && *(volatile int*)&s_n[2] <= BP_QUEUE - 64 * NWAVE) {
+        const int4 item = s_item[it];
+        const unsigned key = (unsigned)__builtin_amdgcn_readfirstlane(item.x);
+        const int ext = __builtin_amdgcn_readfirstlane(item.w);
+        const int wu = ext & 0xffff, cand = wu * (ext >> 16);
+        const double* __restrict__ R = rots + 9LL * (key >> 6);
+        const int4 cp = s_copy[key & 63u];
+        const int c = c0 + lane;
+        const int vr = (int)(((float)c + 0.5f) * (1.0f / (float)wu));  // c < 2^16: exact quotient
+        const int u = item.y + (c - vr * wu), v = item.z + vr;
+        const float fu = (float)u, fv = (float)v;
+        bool in = c < cand;
+        const int g0[3] = {cp.x, cp.y, cp.z};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const float q = (float)g0[a] + 0.5f * (float)(e[a] - 1);
+          const float dc = fmaf((float)R[3 * a], fu, fmaf((float)R[3 * a + 1], fv, -q));
+          in = in && fabsf(dc) <= (float)hw[a] + 0.01f;  // |c| < 3000: the fp32 error is below 0.002
+        }
+        const unsigned long long hit = __ballot(in);
+        int at = 0;
+        if (lane == 0 && hit) at = atomicAdd(&s_n[2], __popcll(hit));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (in)
+          s_queue[at + __popcll(hit & ((1ull << lane) - 1ull))] =
+              make_uint2(key, (unsigned)(u & 0xffff) | ((unsigned)(v & 0xffff) << 16));
+        c0 += 64;
+        if (c0 >= cand) {
+          c0 = 0;
+          it += NWAVE;
+        }
+      }
+      if (it < items && lane == 0) atomicAdd(&s_n[3], 1);
+      __syncthreads();
+      const int qn = s_n[2], left = s_n[3];
+      if (quick)
+        for (int i = tid; i < qn; i += BP_NT) spread(s_queue[i], std::true_type());
+      else
+        for (int i = tid; i < qn; i += BP_NT) spread(s_queue[i], std::false_type());
+      __syncthreads();
+      if (left == 0) break;  // block-uniform
+      if (tid < 2) s_n[2 + tid] = 0;
+      __syncthreads();
+    }
+  }
+  // ---- w = N and b = num / N of the tile's points (the sums of other images added)
+  const double r0 = 1.0 / s0, r1 = 1.0 / s1, r2 = 1.0 / s2;
+  const bool more = *other != 0ull;
+  for (int i = tid; i < T * T * T; i += BP_NT) {
+    const int x = i % T, y = (i / T) % T, z = i / (T * T);
+    if (x >= e[0] || y >= e[1] || z >= e[2]) continue;
+    const long long at = ((long long)(t0[2] + z) * d.ny + (t0[1] + y)) * d.nx + (t0[0] + x);
+    unsigned long long a0 = s_acc[0][z * ZP + y * YP + x], a1 = s_acc[1][z * ZP + y * YP + x],
+                       a2 = s_acc[2][z * ZP + y * YP + x];
+    if (more) {
+      a0 += acc[at];
+      a1 += acc[d.nvox + at];
+      a2 += acc[2 * d.nvox + at];
+    }
+    const double den = (double)(long long)a2 * r2;
+    const double nr = (double)(long long)a0 * r0, ni = (double)(long long)a1 * r1;
+    w[at] = (float)den;
+    b[at] = den > 0 ? make_float2((float)(nr / den), (float)(ni / den)) : make_float2(0.f, 0.f);
+  }
 }
 
 struct RedOps {
@@ -3091,23 +3415,52 @@ hipError_t launch_expand_bbar(const Dims& d, const float2* S, const float* w, fl
   return hipGetLastError();
 }
 
+// Tiles where every axis has at least 16 points (below, tiles are few and mostly halo), a
+// tile has at most 4 copies per axis within reach (m <= 2 n), image and copy fit the 31 bits
+// of a queue entry, 1 / h is finite, and the workspace holds the flag word (it is rounded up
+// to 256 bytes, which leaves room for it unless nvox % 32 == 31).
+static bool bp_tiled(const Dims& d, int n_img, int m, double h, size_t bytes) {
+  const int nmin = d.nx < d.ny ? (d.nx < d.nz ? d.nx : d.nz) : (d.ny < d.nz ? d.ny : d.nz);
+  return nmin >= 16 && m <= 2 * nmin && n_img < (1 << 25) && h >= 1e-300 && (size_t)(3 * d.nvox + 4) * 8 <= bytes;
+}
+
 hipError_t launch_backproject(const Dims& d, int n_img, int m, const float2* images, const double* rots,
-                              const float* ctf, const float* weights, double h, void* ws, float* w, float2* b,
-                              hipStream_t st) {
-  // workspace: 3 nvox fixed-point sums, then the 3 term maxima (all zero bits to start)
+                              const float* ctf, const float* weights, double h, void* ws, size_t bytes, float* w,
+                              float2* b, hipStream_t st) {
+  // workspace: 3 nvox fixed-point sums, the 3 term maxima and (tiles) whether any image's
+  // matrix is not a rotation
   unsigned long long* acc = static_cast<unsigned long long*>(ws);
   unsigned long long* mx = acc + 3 * d.nvox;
-  k_fill_f64<<<ew_grid(3 * d.nvox + 3), 256, 0, st>>>(static_cast<double*>(ws), 3 * d.nvox + 3);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  const bool tiled = bp_tiled(d, n_img, m, h, bytes);
+  unsigned long long* other = tiled ? mx + 3 : nullptr;
+  hipError_t e;
+  if (tiled) k_fill_f64<<<1, 64, 0, st>>>(reinterpret_cast<double*>(mx), 4, nullptr);
+  else k_fill_f64<<<ew_grid(3 * d.nvox + 3), 256, 0, st>>>(static_cast<double*>(ws), 3 * d.nvox + 3, nullptr);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   const long long total = (long long)n_img * m * m;
   long long g = (total + 255) / 256;
   if (g > 65536) g = 65536;
-  k_bp_max<<<(unsigned)(g < 1024 ? g : 1024), 256, 0, st>>>(n_img, m, images, ctf, weights, mx);
+  const long long gm = (total + BP_MAX_NT - 1) / BP_MAX_NT;
+  k_bp_max<<<(unsigned)(gm < 256 ? gm : 256), BP_MAX_NT, 0, st>>>(n_img, m, images, rots, ctf, weights, mx, other);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_backproject<<<(unsigned)g, 256, 0, st>>>(d, n_img, m, images, rots, ctf, weights, h, acc, mx);
+  if (tiled) {
+    k_fill_f64<<<ew_grid(3 * d.nvox), 256, 0, st>>>(static_cast<double*>(ws), 3 * d.nvox, other);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  k_backproject<<<(unsigned)g, 256, 0, st>>>(d, n_img, m, images, rots, ctf, weights, h, acc, mx, other);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_backproject_final<<<ew_grid(d.nvox), 256, 0, st>>>(d.nvox, total, acc, mx, w, b);
+  if (tiled) {
+    // 8^3 tiles, or 4^3 where those would be fewer than two per CU
+    auto tiles = [&](int T) { return (long long)((d.nx + T - 1) / T) * ((d.ny + T - 1) / T) * ((d.nz + T - 1) / T); };
+    if (tiles(8) >= 512)
+      k_bp_tiles<8><<<(unsigned)tiles(8), BP_NT, 0, st>>>(d, n_img, m, images, rots, ctf, weights, 1.0 / h, acc, mx,
+                                                          other, w, b);
+    else
+      k_bp_tiles<4><<<(unsigned)tiles(4), BP_NT, 0, st>>>(d, n_img, m, images, rots, ctf, weights, 1.0 / h, acc, mx,
+                                                          other, w, b);
+  } else {
+    k_backproject_final<<<ew_grid(d.nvox), 256, 0, st>>>(d.nvox, total, acc, mx, w, b);
+  }
   return hipGetLastError();
 }
 
