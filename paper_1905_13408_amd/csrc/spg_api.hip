@@ -24,8 +24,7 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int kStatBlocks = 1024;           // grid of the input-check / reweight kernels
 constexpr int kPartials = 262144;           // fp64 partials in the workspace
-constexpr int kPartA = 0;                   // z-pass objective partials (<= 8192 blocks)
-constexpr int kPartB = 8192;                // kx = 0 / nx/2 plane partials (<= 257 blocks)
+constexpr int kPartA = 0;                   // z-pass objective partials (<= 4096 blocks + 257 of the packed plane)
 constexpr int kPartC = 16384;               // stencil partials: check 6 x <= 8192, monitor 3 x <= 65536
 constexpr int kHistCap = 4096;              // monitored objectives kept (a ring)
 constexpr uint64_t kStateMagic = 0x5350475354415431ull;  // "SPGSTAT1"
@@ -39,7 +38,7 @@ bool pow2_in(int n, int lo, int hi) { return n >= lo && n <= hi && (n & (n - 1))
 bool axis_ok(int n) { return pow2_in(n, 4, 512) || n == 160 || n == 192; }
 
 struct Layout {
-  size_t xhi[3], xlo[3], u, v, S, rbuf, xprev, ws, w0p, wnyq, cs, c0p, cnyq, tw_m, tw_n, tw_y, tw_z, part, res, hist,
+  size_t xhi[3], xlo[3], u, v, S, rbuf, xprev, ws, wnyq, cs, cnyq, tw_m, tw_n, tw_y, tw_z, part, res, hist,
       total;
 };
 
@@ -63,10 +62,8 @@ Layout make_layout(const spg_params& p) {
   L.rbuf = take(nvox * rbytes);
   L.xprev = take(nvox * 4);
   L.ws = take((size_t)p.nz * p.ny * P * 4);
-  L.w0p = take((size_t)p.nz * p.ny * 4);
   L.wnyq = take((size_t)p.nz * p.ny * 4);
   L.cs = take((size_t)p.nz * p.ny * P * 8);
-  L.c0p = take((size_t)p.nz * p.ny * 8);
   L.cnyq = take((size_t)p.nz * p.ny * 8);
   L.tw_m = take(P * 8);
   L.tw_n = take((size_t)p.nx * 8);
@@ -284,23 +281,23 @@ spg_status read_results(spg_problem* P, double* host, int n) {
   return SPG_OK;
 }
 
+FoldedData folded(spg_problem* P) {
+  return {P->at<float>(P->lay.ws), P->at<float2>(P->lay.cs), P->at<float>(P->lay.wnyq), P->at<float2>(P->lay.cnyq)};
+}
+
 // The y, z passes with the weight step on the x-spectrum rows in S (the forward x
 // transform of y already done), the y inverse and, unless x_inverse is false, the x
 // inverse into gout.  obj: also collect the data-term partials.
-spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, int* nB, void* gout, bool gout_bf16,
-                             bool x_inverse = true) {
+spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, void* gout, bool gout_bf16, bool x_inverse = true) {
   const Dims& d = P->d;
   hipStream_t st = P->stream;
   const float2* twy = P->at<float2>(P->lay.tw_y);
   const float2* twz = P->at<float2>(P->lay.tw_z);
-  const float* wsp = P->at<float>(P->lay.ws);
-  const float2* csp = P->at<float2>(P->lay.cs);
+  const FoldedData fd = folded(P);
   if (!obj && yz_plane_supported(d)) {
-    // small maps: the y, z (with the weight step and the packed plane) and y inverse passes
-    // in one launch, timed as the z pass
+    // small maps: the y, z and y inverse passes in one launch, timed as the z pass
     prof_begin(P, SPG_KERNEL_FFT_Z_WEIGHT);
-    SPG_CK(P, launch_yz_plane(d, P->S(), twy, twz, wsp, csp, P->at<float>(P->lay.w0p), P->at<float>(P->lay.wnyq),
-                              P->at<float2>(P->lay.c0p), P->at<float2>(P->lay.cnyq), st));
+    SPG_CK(P, launch_yz_plane(d, P->S(), twy, twz, fd, st));
     prof_end(P, SPG_KERNEL_FFT_Z_WEIGHT);
   } else {
     // Where the spectrum outgrows the 256 MiB last-level cache, the y, z, y passes run on four
@@ -312,22 +309,22 @@ spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, int* nB, void* g
     for (int c = 0; c < nch; ++c) {
       const int kx0 = c * cw, nkx = nch > 1 ? cw : 0;
       prof_begin(P, SPG_KERNEL_FFT_Y_FWD);
-      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, twy, nullptr, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx));
+      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, twy, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx));
       prof_end(P, SPG_KERNEL_FFT_Y_FWD);
       prof_begin(P, SPG_KERNEL_FFT_Z_WEIGHT);
       // the objective variant writes one partial per block: 16-column tiles keep <= 8192 blocks
-      SPG_CK(P, launch_fft_cols(d, P->S(), 2, obj ? 3 : 2, twz, wsp, csp, obj ? P->part() + kPartA : nullptr, st, nA,
+      SPG_CK(P, launch_fft_cols(d, P->S(), 2, obj ? 3 : 2, twz, &fd, obj ? P->part() + kPartA : nullptr, st, nA,
                                 obj ? 16 : P->nt_z, !P->shared_gpu, kx0, nkx));
       prof_end(P, SPG_KERNEL_FFT_Z_WEIGHT);
-      if (c == 0) {  // the packed kx = 0 / nx/2 plane
+      if (c == 0 && dc_plane_apart(d, obj)) {  // the packed kx = 0 / nx/2 plane
+        int nB = 0;
         prof_begin(P, SPG_KERNEL_DC_NYQUIST);
-        SPG_CK(P, launch_dc_nyquist(d, P->S(), twz, P->at<float>(P->lay.w0p), P->at<float>(P->lay.wnyq),
-                                    P->at<float2>(P->lay.c0p), P->at<float2>(P->lay.cnyq),
-                                    obj ? P->part() + kPartB : nullptr, st, nB));
+        SPG_CK(P, launch_dc_nyquist(d, P->S(), twz, fd, obj ? P->part() + kPartA + *nA : nullptr, st, &nB));
         prof_end(P, SPG_KERNEL_DC_NYQUIST);
+        if (nA) *nA += nB;  // its partials follow the z pass's
       }
       prof_begin(P, SPG_KERNEL_FFT_Y_INV);
-      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, twy, nullptr, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx));
+      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, twy, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx));
       prof_end(P, SPG_KERNEL_FFT_Y_INV);
     }
   }
@@ -468,9 +465,8 @@ spg_status spg_set_data(spg_problem* P, const float* d_w, const float* d_b) {
   if (r[0] > 0) return set_err(P, SPG_E_NONFINITE, "w or b holds NaN/Inf values");
   if (r[1] < 0) return set_err(P, SPG_E_INVAL, "negative Fourier weight");
   // 2. fold onto the packed half spectrum
-  SPG_CK(P, launch_fold(d, d_w, b, P->at<float>(P->lay.ws), P->at<float>(P->lay.w0p), P->at<float>(P->lay.wnyq),
-                        P->at<float2>(P->lay.cs), P->at<float2>(P->lay.c0p), P->at<float2>(P->lay.cnyq), part,
-                        kStatBlocks, P->stream));
+  SPG_CK(P, launch_fold(d, d_w, b, P->at<float>(P->lay.ws), P->at<float>(P->lay.wnyq), P->at<float2>(P->lay.cs),
+                        P->at<float2>(P->lay.cnyq), part, kStatBlocks, P->stream));
   const int ops1[1] = {RED_OP_MAX};
   SPG_CK(P, launch_reduce(part, kStatBlocks, 1, ops1, P->res(), P->stream));
   double mx;
@@ -571,8 +567,8 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
     // the objective monitor: F_eps(y_j) from partials of the z pass, the kx = 0 / nx/2 plane
     // and the stencil kernel of this iteration
     const bool mon = P->mon_every > 0 && !capture_g && P->j % P->mon_every == 0;
-    int nA = 0, nB = 0, nC = 0;
-    if ((s = gradient_pipeline(P, mon, &nA, &nB, P->rbuf(), P->bf(), !fuse))) return s;
+    int nA = 0, nC = 0;
+    if ((s = gradient_pipeline(P, mon, &nA, P->rbuf(), P->bf(), !fuse))) return s;
     if (capture_g)
       SPG_CK(P, hipMemcpyAsync(capture_g, P->rbuf(), (size_t)d.nvox * 4, hipMemcpyDeviceToDevice, P->stream));
     const double t_next = P->prm.accel ? 0.5 * (1.0 + std::sqrt(1.0 + 4.0 * P->t * P->t)) : 1.0;
@@ -599,7 +595,7 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
     prof_end(P, SPG_KERNEL_PROX_TV);
     if (mon) {
       const int slot = (int)(P->hist_n % kHistCap);
-      SPG_CK(P, launch_obj_finish(P->part() + kPartA, nA, P->part() + kPartB, nB, P->part() + kPartC, nC, P->C0,
+      SPG_CK(P, launch_obj_finish(P->part() + kPartA, nA, P->part() + kPartC, nC, P->C0,
                                   P->prm.lambda, P->prm.mu, P->prm.gamma, P->at<double>(P->lay.hist) + slot,
                                   P->stream));
       P->hist_iter[slot] = P->iters_done + 1;
@@ -718,8 +714,8 @@ spg_status spg_final_check(spg_problem* P, double* F_eps, double* F_0, double* k
   const int spare = 3 - P->cur - P->old;
   P->primed = false;
   if ((s = r2c(P, P->xhi(P->cur), false))) return s;
-  int nA = 0, nB = 0;
-  if ((s = gradient_pipeline(P, true, &nA, &nB, P->xhi(spare), false))) return s;
+  int nA = 0;
+  if ((s = gradient_pipeline(P, true, &nA, P->xhi(spare), false))) return s;
   ProxArgs a = prox_args(P, P->cur, 0.0, 0.0);
   a.read_old = 0;
   a.gin = P->xhi(spare);
@@ -733,15 +729,14 @@ spg_status spg_final_check(spg_problem* P, double* F_eps, double* F_0, double* k
   const int sum1[1] = {RED_OP_SUM};
   const int sum6[6] = {RED_OP_SUM, RED_OP_SUM, RED_OP_SUM, RED_OP_SUM, RED_OP_SUM, RED_OP_SUM};
   SPG_CK(P, launch_reduce(P->part() + kPartA, nA, 1, sum1, P->res() + 0, P->stream));
-  SPG_CK(P, launch_reduce(P->part() + kPartB, nB, 1, sum1, P->res() + 1, P->stream));
-  SPG_CK(P, launch_reduce(P->part() + kPartC, nC, 6, sum6, P->res() + 2, P->stream));
-  double r[8];
-  if ((s = read_results(P, r, 8))) return s;
-  const double data = P->C0 + r[0] + r[1];
-  const double prior = P->prm.gamma * r[7];
-  const double fe = data + P->prm.lambda * r[2] + P->prm.mu * r[3] + prior;
-  const double f0 = data + P->prm.lambda * r[2] + P->prm.mu * r[4] + prior;
-  const double kkt = std::sqrt(r[5]) / (r[6] > 0 ? std::sqrt(r[6]) : 1.0);
+  SPG_CK(P, launch_reduce(P->part() + kPartC, nC, 6, sum6, P->res() + 1, P->stream));
+  double r[7];
+  if ((s = read_results(P, r, 7))) return s;
+  const double data = P->C0 + r[0];
+  const double prior = P->prm.gamma * r[6];
+  const double fe = data + P->prm.lambda * r[1] + P->prm.mu * r[2] + prior;
+  const double f0 = data + P->prm.lambda * r[1] + P->prm.mu * r[3] + prior;
+  const double kkt = std::sqrt(r[4]) / (r[5] > 0 ? std::sqrt(r[5]) : 1.0);
   if (F_eps) *F_eps = fe;
   if (F_0) *F_0 = f0;
   if (kkt_rel) *kkt_rel = kkt;
@@ -780,18 +775,17 @@ spg_status spg_log_objective(spg_problem* P, double eps1, double eps2, double* G
   const int spare = 3 - P->cur - P->old;
   P->primed = false;
   if ((s = r2c(P, P->xhi(P->cur), false))) return s;
-  int nA = 0, nB = 0;
-  if ((s = gradient_pipeline(P, true, &nA, &nB, P->xhi(spare), false))) return s;
+  int nA = 0;
+  if ((s = gradient_pipeline(P, true, &nA, P->xhi(spare), false))) return s;
   SPG_CK(P, launch_log_terms(P->d, P->xhi(P->cur), P->xlo(P->cur), eps1, eps2, P->comp, P->part() + kPartC,
                              kStatBlocks, P->stream));
   const int sum1[1] = {RED_OP_SUM};
   const int sum2[2] = {RED_OP_SUM, RED_OP_SUM};
   SPG_CK(P, launch_reduce(P->part() + kPartA, nA, 1, sum1, P->res() + 0, P->stream));
-  SPG_CK(P, launch_reduce(P->part() + kPartB, nB, 1, sum1, P->res() + 1, P->stream));
-  SPG_CK(P, launch_reduce(P->part() + kPartC, kStatBlocks, 2, sum2, P->res() + 2, P->stream));
-  double r[4];
-  if ((s = read_results(P, r, 4))) return s;
-  *G = P->C0 + r[0] + r[1] + P->prm.lambda * r[2] + P->prm.mu * r[3];
+  SPG_CK(P, launch_reduce(P->part() + kPartC, kStatBlocks, 2, sum2, P->res() + 1, P->stream));
+  double r[3];
+  if ((s = read_results(P, r, 3))) return s;
+  *G = P->C0 + r[0] + P->prm.lambda * r[1] + P->prm.mu * r[2];
   if (!std::isfinite(*G)) return set_err(P, SPG_E_DIVERGED, "log objective is not finite");
   return SPG_OK;
 }
@@ -866,9 +860,9 @@ spg_status fsc_run(int nx, int ny, int nz, const float* d_map1, const float* d_m
   float2* specs[2] = {reinterpret_cast<float2*>(ws + lay.S1), reinterpret_cast<float2*>(ws + lay.S2)};
   for (int k = 0; k < 2; ++k) {
     if (launch_r2c_x(d, maps[k], false, specs[k], tw[0], tw[1], st) != hipSuccess) return SPG_E_DEVICE;
-    if (launch_fft_cols(d, specs[k], 1, 0, tw[2], nullptr, nullptr, nullptr, st, nullptr) != hipSuccess)
+    if (launch_fft_cols(d, specs[k], 1, 0, tw[2], nullptr, nullptr, st, nullptr) != hipSuccess)
       return SPG_E_DEVICE;
-    if (launch_fft_cols(d, specs[k], 2, 0, tw[3], nullptr, nullptr, nullptr, st, nullptr) != hipSuccess)
+    if (launch_fft_cols(d, specs[k], 2, 0, tw[3], nullptr, nullptr, st, nullptr) != hipSuccess)
       return SPG_E_DEVICE;
   }
   double* out = reinterpret_cast<double*>(ws + lay.out);
@@ -1393,12 +1387,13 @@ spg_status hessian_data(spg_problem* P, const float* in, float* out) {
   const Dims& d = P->d;
   hipStream_t st = P->stream;
   SPG_CK(P, launch_r2c_x(d, in, false, P->S(), P->at<float2>(P->lay.tw_m), P->at<float2>(P->lay.tw_n), st));
-  SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, P->at<float2>(P->lay.tw_y), nullptr, nullptr, nullptr, st, nullptr));
-  SPG_CK(P, launch_fft_cols(d, P->S(), 2, 4, P->at<float2>(P->lay.tw_z), P->at<float>(P->lay.ws), nullptr, nullptr,
-                            st, nullptr));
-  SPG_CK(P, launch_dc_nyquist(d, P->S(), P->at<float2>(P->lay.tw_z), P->at<float>(P->lay.w0p),
-                              P->at<float>(P->lay.wnyq), nullptr, nullptr, nullptr, st, nullptr));
-  SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, P->at<float2>(P->lay.tw_y), nullptr, nullptr, nullptr, st, nullptr));
+  SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, P->at<float2>(P->lay.tw_y), nullptr, nullptr, st, nullptr));
+  FoldedData fd = folded(P);
+  fd.cs = fd.cnyq = nullptr;
+  SPG_CK(P, launch_fft_cols(d, P->S(), 2, 4, P->at<float2>(P->lay.tw_z), &fd, nullptr, st, nullptr));
+  if (dc_plane_apart(d, false))
+    SPG_CK(P, launch_dc_nyquist(d, P->S(), P->at<float2>(P->lay.tw_z), fd, nullptr, st, nullptr));
+  SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, P->at<float2>(P->lay.tw_y), nullptr, nullptr, st, nullptr));
   SPG_CK(P, launch_c2r_x(d, P->S(), out, false, P->at<float2>(P->lay.tw_m), P->at<float2>(P->lay.tw_n), st));
   return SPG_OK;
 }
@@ -1514,8 +1509,8 @@ spg_status spg_vjp(spg_problem* P, void* d_vjp_ws, size_t bytes, const float* d_
   mub += lrb * (-lr * lr * P->vmax * P->dn2 / P->prm.eps);
   // b-bar = w * A(rbar)
   SPG_CK(P, launch_r2c_x(d, rbar, false, P->S(), P->at<float2>(P->lay.tw_m), P->at<float2>(P->lay.tw_n), st));
-  SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, P->at<float2>(P->lay.tw_y), nullptr, nullptr, nullptr, st, nullptr));
-  SPG_CK(P, launch_fft_cols(d, P->S(), 2, 0, P->at<float2>(P->lay.tw_z), nullptr, nullptr, nullptr, st, nullptr));
+  SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, P->at<float2>(P->lay.tw_y), nullptr, nullptr, st, nullptr));
+  SPG_CK(P, launch_fft_cols(d, P->S(), 2, 0, P->at<float2>(P->lay.tw_z), nullptr, nullptr, st, nullptr));
   SPG_CK(P, launch_expand_bbar(d, P->S(), d_w, reinterpret_cast<float2*>(d_bbar), st));
   // back to the end state of the unrolled solve
   if ((s = ck_copy(P, ws, L, L.nseg, false))) return s;

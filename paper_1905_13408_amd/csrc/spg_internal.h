@@ -68,22 +68,32 @@ int prox_fft_num_blocks(const Dims& d, int zc);
 hipError_t launch_prox_fft(const Dims& d, const ProxArgs& a, float2* S, const float2* tw_m, const float2* tw_n,
                            int store, hipStream_t st, bool mon = false);
 
+// Folded weights and data terms of the z pass (cs and cnyq null for mode 4): the packed half
+// spectrum's, and those of the plane kx = nx/2 that shares its slot 0 with kx = 0.
+struct FoldedData {
+  const float* ws;
+  const float2* cs;
+  const float* wnyq;
+  const float2* cnyq;
+};
+
 // persist: the fused z modes run persistent blocks (false: one block per tile, for
 // problems that share the GPU with concurrent work).  kx0, nkx: the columns [kx0, kx0 + nkx)
 // of the packed spectrum only (nkx = 0: to the end of the row); the objective mode (3) takes
 // the whole row.
-hipError_t launch_fft_cols(const Dims& d, float2* S, int axis /*1 = y, 2 = z*/, int mode,
-                           const float2* tw, const float* ws, const float2* cs, double* partials,
-                           hipStream_t st, int* nblocks_out, int nt = 16 /* columns per tile: 8 or 16 */,
-                           bool persist = true, int kx0 = 0, int nkx = 0);
+hipError_t launch_fft_cols(const Dims& d, float2* S, int axis /*1 = y, 2 = z*/, int mode, const float2* tw,
+                           const FoldedData* fd /* fused z modes */, double* partials, hipStream_t st,
+                           int* nblocks_out, int nt = 16 /* columns per tile: 8 or 16 */, bool persist = true,
+                           int kx0 = 0, int nkx = 0);
 // Small maps (ny, nz in {8, 16, 32, 64}): the y forward, z + weight + packed-plane and y inverse
 // passes in one launch, one block per (ky, kz) plane of a column kx.
 bool yz_plane_supported(const Dims& d);
-hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const float2* tw_z, const float* ws,
-                           const float2* cs, const float* w0p, const float* wnyq, const float2* c0p,
-                           const float2* cnyq, hipStream_t st);
-hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const float* w0p,
-                             const float* wnyq, const float2* c0p, const float2* cnyq, double* partials,
+hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const float2* tw_z, const FoldedData& fd,
+                           hipStream_t st);
+// Whether the packed plane is left out of the fused z modes (obj: of mode 3) and has a launch
+// of its own.
+bool dc_plane_apart(const Dims& d, bool obj);
+hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const FoldedData& fd, double* partials,
                              hipStream_t st, int* nblocks_out);
 hipError_t launch_r2c_x(const Dims& d, const void* rin, bool rin_bf16, float2* S, const float2* tw_m,
                         const float2* tw_n, hipStream_t st);
@@ -98,8 +108,8 @@ hipError_t launch_prime(const Dims& d, void* rbuf, const float* xk_hi, const uin
 hipError_t launch_set_map(const Dims& d, const float* x0, float* hi, uint16_t* lo, hipStream_t st);
 hipError_t launch_get_map(const Dims& d, const float* hi, const uint16_t* lo, float* out, bool compensated,
                           hipStream_t st);
-hipError_t launch_fold(const Dims& d, const float* w, const float2* b, float* ws, float* w0p, float* wnyq,
-                       float2* cs, float2* c0p, float2* cnyq, double* partials, int nblocks, hipStream_t st);
+hipError_t launch_fold(const Dims& d, const float* w, const float2* b, float* ws, float* wnyq, float2* cs,
+                       float2* cnyq, double* partials, int nblocks, hipStream_t st);
 // partials: 5 x nblocks (non-finite count, min w, 1/2 sum w|b|^2, sum w, energy of the
 // real part of the unregularised solution)
 hipError_t launch_data_stats(const Dims& d, const float* w, const float2* b, double* partials, int nblocks,
@@ -114,9 +124,9 @@ hipError_t launch_reweight(const Dims& d, const float* hi, const uint16_t* lo, v
 hipError_t launch_f32_to_bf16(const float* src, uint16_t* dst, long long n, hipStream_t st);
 hipError_t launch_bf16_to_f32(const uint16_t* src, float* dst, long long n, hipStream_t st);
 hipError_t launch_fill(float* dst, long long n, float value, hipStream_t st);
-// out = c0 + sum pa[na] + sum pb[nb] + lam sum pc[0:nc] + mu sum pc[nc:2nc] + gamma sum pc[2nc:3nc]
-hipError_t launch_obj_finish(const double* pa, int na, const double* pb, int nb, const double* pc, int nc, double c0,
-                             double lam, double mu, double gamma, double* out, hipStream_t st);
+// out = c0 + sum pa[na] + lam sum pc[0:nc] + mu sum pc[nc:2nc] + gamma sum pc[2nc:3nc]
+hipError_t launch_obj_finish(const double* pa, int na, const double* pc, int nc, double c0, double lam, double mu,
+                             double gamma, double* out, hipStream_t st);
 hipError_t launch_reduce(const double* partials, int n, int nq, const int* ops, double* out, hipStream_t st);
 hipError_t launch_adj_prox(const Dims& d, const float* xn, const float* abar, const float* gdat, const float* u,
                            float lr, float* zbar, float* rbar, double* partials, int nblocks, hipStream_t st);

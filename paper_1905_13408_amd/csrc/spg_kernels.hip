@@ -5,7 +5,8 @@
 // spectrum S except where noted):
 //   k_fft_cols<mode 0> (y axis)   forward column FFTs along y
 //   k_fft_zw<mode 2>   (z axis)   forward FFT along z, G = w~ Y - c, inverse FFT along z
-//   k_dc_nyquist                  the same for the packed kx = 0 / kx = nx/2 plane
+//                                 (the packed kx = 0 / kx = nx/2 plane with its partners -k;
+//                                 on 512-point z axes in k_dc_nyquist)
 //   k_fft_cols<mode 1> (y axis)   inverse column FFTs along y
 //   k_c2r_x                       x-axis inverse real FFT -> data gradient map
 //   k_prox_tv                     smoothed-TV stencil, gradient step, soft threshold,
@@ -540,7 +541,7 @@ __device__ double block_reduce(double v, double* sh) {
 // k_fft_cols, one tile per block -- mode 0: forward; mode 1: inverse.
 // k_fft_zw, persistent blocks on the z axis -- mode 2: forward, G = ws*Y - cs, inverse;
 // mode 3: as 2 and also writes per-block partials of 1/2 ws |Y|^2 - Re(conj(cs) Y)
-// (multiplicity 2 for 0 < kx < nx/2; the kx = 0 column is done by k_dc_nyquist);
+// (multiplicity 2 for 0 < kx < nx/2; the kx = 0 column where k_dc_nyquist does not do it);
 // mode 4: forward, G = ws*Y, inverse (the data-term Hessian applied to a map).
 
 // Element access at a 32-bit byte offset from a block-uniform base pointer.
@@ -619,14 +620,93 @@ __global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_cols(float2* __restrict
 // NTW: the folded weight and data term arrive by streaming loads (maps where they outgrow
 // the last-level cache; smaller maps keep them cached from one iteration to the next).
 // S and P describe the columns of this launch (a range of kx starting at column kxo of the
-// spectrum); Pw is the full row width, which lays out the folded weight and data term.
+// spectrum, whole tiles of NT); Pw is the full row width, which lays out the folded weight
+// and data term.
+//
+// The packed kx = 0 / kx = nx/2 plane: the slot holds Z = X0 + i XN where X0 and XN are the
+// (complex) yz spectra of the real x-axis planes kx = 0 and kx = nx/2.  Both are Hermitian in
+// (ky, kz), so X0(k) = (Z(k) + conj Z(-k))/2 and XN(k) = (Z(k) - conj Z(-k))/(2i): the column
+// kx = 0 of ky needs that of -ky at its weight step.  The two units of the first tile that the
+// rows ky and -ky would have are therefore cut the other way: one takes the first H = NT/2
+// columns of both rows, the other the last H (rows 0 and ny/2, their own partners, form one
+// pair): same work per unit and no launch of its own for the plane (ZP_PAIR).
+// That takes registers, so on axes of 256 points, whose blocks have none to spare, whole
+// column pairs run as the first blocks of the launch instead (ZP_RIDE, dc_pairs), one block
+// per tile in place of persistent blocks; on 512-point axes, where they would run as a second
+// round behind one persistent block per CU, the plane has its own launch (ZP_APART,
+// k_dc_nyquist, 14.5 us of 1560 per iteration).  z pass with the plane, apart / riding /
+// paired: 128^3 20.5 / 16.4 / 11.0 us, 256^3 55 / 44.5 / 60 us, 512^3 385 / - / 434 us.
+enum { ZP_PAIR, ZP_RIDE, ZP_APART };
+template <int L>
+struct ZPlane {
+  static constexpr int value = L < 256 ? ZP_PAIR : (L == 256 ? ZP_RIDE : ZP_APART);
+};
+
+// ZP_RIDE: thread (c, q) holds column c & 1 of the block's pair c / 2, points q + T i.
+template <int L, bool DATA>
+__device__ __forceinline__ void dc_pairs(float2* __restrict__ S, int P, int ny, long long pstride,
+                                         const float2* __restrict__ tw, const float* __restrict__ ws,
+                                         const float2* __restrict__ cs, const float* __restrict__ wnyq,
+                                         const float2* __restrict__ cnyq, float* s_re, float* s_im, float2* s_tw,
+                                         int NT, int c, int q) {
+  constexpr int T = ColT<L>::T;
+  constexpr int E = RegPlan<L, T>::E;
+  const int pair = (int)blockIdx.x * (NT >> 1) + (c >> 1);
+  const int ky = min(pair, ny / 2);  // past the last pair: that one again, not stored
+  const int kyp = ky == 0 ? 0 : ny - ky;
+  const int myky = (c & 1) ? kyp : ky;
+  const int WG = P < 16 ? P : 16;
+  float2* __restrict__ Sc = S + (long long)myky * P;
+  float2 a[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) a[i] = Sc[(long long)(q + T * i) * pstride];
+  for (int i = threadIdx.x; i < L; i += blockDim.x) s_tw[i] = tw[i];
+  __syncthreads();
+  float* re = s_re + c;
+  float* im = s_im + c;
+  fft_reg<L, false, T>(a, re, im, NT, q, s_tw);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    re[(q + T * i) * NT] = a[i].x;
+    im[(q + T * i) * NT] = a[i].y;
+  }
+  __syncthreads();
+  const float* pre = s_re + (c ^ 1);
+  const float* pim = s_im + (c ^ 1);
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const int kz = q + T * i, kzp = kz == 0 ? 0 : L - kz;
+    const long long o = (long long)myky * L + kz;
+    const long long o0 = ((long long)myky * (P / WG) * L + kz) * WG;  // kx = 0 of the folded layout
+    const float w0 = ws[o0], wn = wnyq[o];
+    float2 c0 = make_float2(0.f, 0.f), cn = c0;
+    if constexpr (DATA) {
+      c0 = cs[o0];
+      cn = cnyq[o];
+    }
+    const float2 z1 = a[i], z2 = make_float2(pre[kzp * NT], pim[kzp * NT]);
+    const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
+    const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
+    const float2 B = make_float2(dd.y, -dd.x);
+    const float2 g0 = make_float2(w0 * A.x - c0.x, w0 * A.y - c0.y);
+    const float2 gn = make_float2(wn * B.x - cn.x, wn * B.y - cn.y);
+    a[i] = make_float2(g0.x - gn.y, g0.y + gn.x);
+  }
+  __syncthreads();
+  fft_reg<L, true, T>(a, re, im, NT, q, s_tw);
+  if (pair <= ny / 2 && ((c & 1) == 0 || ky != kyp)) {
+#pragma unroll
+    for (int i = 0; i < E; ++i) Sc[(long long)(q + T * i) * pstride] = a[i];
+  }
+}
+
+// ride: leading blocks of the launch that do the packed plane (ZP_RIDE).
 template <int L, int MODE, bool NTW = false>
-__global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_zw(float2* __restrict__ S, int P, int ntiles, int total,
-                                                              long long pstride, long long bstride,
-                                                              const float2* __restrict__ tw,
-                                                              const float* __restrict__ ws,
-                                                              const float2* __restrict__ cs,
-                                                              double* __restrict__ partials, int NT, int Pw, int kxo) {
+__global__ void __launch_bounds__(16 * ColT<L>::T)
+    k_fft_zw(float2* __restrict__ S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
+             const float2* __restrict__ tw, const float* __restrict__ ws, const float2* __restrict__ cs,
+             const float* __restrict__ wnyq, const float2* __restrict__ cnyq, double* __restrict__ partials, int NT, int Pw, int kxo, int ride) {
   __shared__ float s_re[L * 16];
   __shared__ float s_im[L * 16];
   __shared__ float2 s_tw[L];
@@ -636,46 +716,69 @@ __global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_zw(float2* __restrict__
   const int tid = threadIdx.x;
   const int c = tid % NT, q = tid / NT;
   static_assert(MODE >= 2 && MODE <= 4, "fused z modes");
+  constexpr bool PAIR = ZPlane<L>::value == ZP_PAIR;
+  if constexpr (ZPlane<L>::value == ZP_RIDE && MODE != 3) {
+    if ((int)blockIdx.x < ride) {
+      dc_pairs<L, MODE != 4>(S, Pw, ny, pstride, tw, ws, cs, wnyq, cnyq, s_re, s_im, s_tw, NT, c, q);
+      return;
+    }
+  }
   // Persistent blocks that load the next tile while transforming the current one: with a
   // grid of 8k blocks, XCD x (= blockIdx % 8) owns the contiguous tile range
   // [x chunk, (x+1) chunk) and its k-th block walks that range with stride k, so tiles
   // that share 128-byte lines (the folded weight rows of neighbouring 16-column tiles)
   // are in flight in one L2 at the same time.
-  const int G = gridDim.x;
+  const int G = gridDim.x - ride, bid = blockIdx.x - ride;
   const bool split = G >= 8 && (G & 7) == 0;
-  const int xcd = split ? (int)(blockIdx.x & 7u) : 0;
+  const int xcd = split ? bid & 7 : 0;
   const int chunk = split ? (total + 7) >> 3 : total;
   const int nb = split ? G >> 3 : G;
-  int t = xcd * chunk + (split ? (int)(blockIdx.x >> 3) : (int)blockIdx.x);
+  int t = xcd * chunk + (split ? bid >> 3 : bid);
   const int t_end = min(total, xcd * chunk + chunk);
   // Block-uniform tile base pointers and unsigned 32-bit per-lane byte offsets of the
   // complex elements (every offset in a column is below nz*ny*P*8 <= 2^29 bytes), so the
   // loads take a scalar base and a 32-bit vector offset; the fp32 weight uses half the
-  // offset.  A lane whose column lies past the last kx reads column 0 of its tile instead
-  // (always in bounds) and stores nothing.
+  // offset.
+  const int H = NT >> 1;
   const unsigned ps = (unsigned)pstride;
   const unsigned step = (unsigned)T * ps * 8u;
-  auto tile_base = [&](int tt) -> long long {
-    return (long long)(tt / ntiles) * bstride + (long long)(tt % ntiles) * NT;
+  // a unit's first row and column, and the distance to the other row of a pair (0: no pair)
+  auto place = [&](int tt, int& ky, int& kx, int& dk) {
+    const int r = tt / ntiles, tile = tt - r * ntiles;
+    if (PAIR && tile == 0 && kxo == 0) {
+      ky = r >> 1;
+      kx = (r & 1) * H;
+      dk = ky == 0 ? ny >> 1 : ny - 2 * ky;
+    } else {
+      ky = r;
+      kx = tile * NT;
+      dk = 0;
+    }
   };
-  auto lane_off = [&](int tt) -> unsigned {
-    return ((unsigned)((tt % ntiles) * NT + c < P ? c : 0) + (unsigned)q * ps) * 8u;
+  auto lane_off = [&](int dk, int c, int q) -> unsigned {
+    const unsigned col = dk && c >= H ? (unsigned)(c - H) + (unsigned)dk * (unsigned)bstride : (unsigned)c;
+    return (col + (unsigned)q * ps) * 8u;
   };
+  auto base_of = [&](int ky, int kx) -> long long { return (long long)ky * bstride + kx; };
   // folded weight / data term: tile-major groups of WG = min(16, Pw) columns along z
   const int WG = Pw < 16 ? Pw : 16;
-  auto wc_base = [&](int tt) -> long long {
-    const int kx0 = kxo + (tt % ntiles) * NT;
-    return ((long long)(tt / ntiles) * (Pw / WG) + kx0 / WG) * L * WG + kx0 % WG;
+  const unsigned wrow = (unsigned)(Pw / WG) * (unsigned)(L * WG);  // elements of one ky
+  auto wc_base = [&](int ky, int kx) -> long long {
+    const int k = kxo + kx;
+    return ((long long)ky * (Pw / WG) + k / WG) * L * WG + k % WG;
   };
-  auto wc_off = [&](int tt) -> unsigned {  // element offset of the lane in its tile
-    return (unsigned)((tt % ntiles) * NT + c < P ? c : 0) + (unsigned)(q * WG);
+  auto wc_off = [&](int dk, int c, int q) -> unsigned {  // element offset of the lane in its tile
+    const unsigned col = dk && c >= H ? (unsigned)(c - H) + (unsigned)dk * wrow : (unsigned)c;
+    return col + (unsigned)(q * WG);
   };
   const unsigned wstep = (unsigned)(T * WG);
 
   float2 a[E];
   if (t < t_end) {
-    const float2* __restrict__ Sb = S + tile_base(t);
-    const unsigned o = lane_off(t);
+    int ky, kx, dk;
+    place(t, ky, kx, dk);
+    const float2* __restrict__ Sb = S + base_of(ky, kx);
+    const unsigned o = lane_off(dk, c, q);
 #pragma unroll
     for (int i = 0; i < E; ++i) a[i] = ld_at(Sb, o + i * step);
   }
@@ -683,25 +786,23 @@ __global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_zw(float2* __restrict__
   double acc = 0.0;
   for (; t < t_end; t += nb) {
     __syncthreads();  // twiddles visible; the previous tile's last stage read the LDS planes
-    // The lane indices pass through an empty asm statement so that the per-stage LDS
-    // addresses derived from them are formed inside the loop where they are used, not
+    // The lane indices pass through an empty asm statement so that the per-stage LDS and the
+    // global addresses derived from them are formed inside the loop where they are used, not
     // hoisted out of it and held in registers across all tiles.
     int cl = c, ql = q;
     asm volatile("" : "+v"(cl), "+v"(ql));
     float* re = s_re + cl;
     float* im = s_im + cl;
-    const long long ub = tile_base(t);
-    const int kx = (t % ntiles) * NT + cl;
-    const bool valid = kx < P;
-    const unsigned o = lane_off(t);
+    int ky, kx, dk;
+    place(t, ky, kx, dk);
     const int tn = t + nb;
     const bool more = tn < t_end;  // block-uniform
     float2 nxt[E];
     float wv[E];
     float2 cv[E];
     // the folded weight and data term load during the forward stages
-    const long long wb = wc_base(t);
-    const unsigned ow = wc_off(t);
+    const long long wb = wc_base(ky, kx);
+    const unsigned ow = wc_off(dk, cl, ql);
     const float* __restrict__ wsb = ws + wb;
 #pragma unroll
     for (int i = 0; i < E; ++i) wv[i] = ld_nt<NTW>(wsb, (ow + i * wstep) * 4u);
@@ -715,29 +816,77 @@ __global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_zw(float2* __restrict__
     }
     reg_stages<L, T, 0, false, 1>(a, re, im, NT, ql, s_tw);
     reg_stages<L, T, 1, false>(a, re, im, NT, ql, s_tw);
+    const bool first = PAIR && dk != 0 && kx == 0;            // block-uniform
+    const bool packed = first && (cl == 0 || cl == H);        // lanes of the packed columns
+    if (first) {
+      // the kx = nx/2 terms, all requested before the exchange
+      float wnv[E];
+      float2 cnv[E];
+      if (packed) {
+        const unsigned on = (unsigned)(cl == 0 ? ky : ky + dk) * (unsigned)L + (unsigned)ql;
 #pragma unroll
-    for (int i = 0; i < E; ++i) {
-      const float yr = a[i].x, yi = a[i].y;
-      if constexpr (MODE == 3) {
-        if (valid && kx > 0)
-          acc += 2.0 * (0.5 * (double)wv[i] * ((double)yr * yr + (double)yi * yi) -
-                        ((double)cv[i].x * yr + (double)cv[i].y * yi));
+        for (int i = 0; i < E; ++i) {
+          wnv[i] = ld_at(wnyq, (on + T * i) * 4u);
+          cnv[i] = make_float2(0.f, 0.f);
+          if constexpr (MODE != 4) cnv[i] = ld_at(cnyq, (on + T * i) * 8u);
+        }
       }
-      a[i] = make_float2(wv[i] * yr - cv[i].x, wv[i] * yi - cv[i].y);
+      __syncthreads();  // the forward transform's last stage read the LDS planes
+      if (packed) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          re[(ql + T * i) * NT] = a[i].x;
+          im[(ql + T * i) * NT] = a[i].y;
+        }
+      }
+      __syncthreads();
+      if (packed) {
+        const int cp = ky == 0 ? 0 : (cl == 0 ? H : -H);  // partner column -ky, as an offset
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const int kz = ql + T * i, kzp = kz == 0 ? 0 : L - kz;
+          const float w0 = wv[i], wn = wnv[i];
+          const float2 c0 = cv[i], cn = cnv[i];
+          const float2 z1 = a[i], z2 = make_float2(re[kzp * NT + cp], im[kzp * NT + cp]);
+          const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
+          const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
+          const float2 B = make_float2(dd.y, -dd.x);
+          if constexpr (MODE == 3)
+            acc += 0.5 * (double)w0 * ((double)A.x * A.x + (double)A.y * A.y) - ((double)c0.x * A.x + (double)c0.y * A.y) +
+                   0.5 * (double)wn * ((double)B.x * B.x + (double)B.y * B.y) - ((double)cn.x * B.x + (double)cn.y * B.y);
+          const float2 g0 = make_float2(w0 * A.x - c0.x, w0 * A.y - c0.y);
+          const float2 gn = make_float2(wn * B.x - cn.x, wn * B.y - cn.y);
+          a[i] = make_float2(g0.x - gn.y, g0.y + gn.x);
+        }
+      }
+    }
+    if (!packed) {
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const float yr = a[i].x, yi = a[i].y;
+        if constexpr (MODE == 3) {
+          if (PAIR || kx + cl > 0)
+            acc += 2.0 * (0.5 * (double)wv[i] * ((double)yr * yr + (double)yi * yi) -
+                          ((double)cv[i].x * yr + (double)cv[i].y * yi));
+        }
+        a[i] = make_float2(wv[i] * yr - cv[i].x, wv[i] * yi - cv[i].y);
+      }
     }
     __syncthreads();  // the forward transform's last stage read the LDS planes
     reg_stages<L, T, 0, true, 1>(a, re, im, NT, ql, s_tw);
     // the next tile loads during the remaining inverse stages
     if (more) {
-      const float2* __restrict__ Sn = S + tile_base(tn);
-      const unsigned on = lane_off(tn);
+      int nky, nkx, ndk;
+      place(tn, nky, nkx, ndk);
+      const float2* __restrict__ Sn = S + base_of(nky, nkx);
+      const unsigned on = lane_off(ndk, cl, ql);
 #pragma unroll
       for (int i = 0; i < E; ++i) nxt[i] = ld_at(Sn, on + i * step);
     }
     reg_stages<L, T, 1, true>(a, re, im, NT, ql, s_tw);
-
-    if (valid && kx + kxo != 0) {  // the kx = 0 column belongs to k_dc_nyquist
-      float2* __restrict__ Sb = S + ub;
+    if (PAIR || kx + kxo + cl > 0) {
+      float2* __restrict__ Sb = S + base_of(ky, kx);
+      const unsigned o = lane_off(dk, cl, ql);
 #pragma unroll
       for (int i = 0; i < E; ++i) st_at(Sb, o + i * step, a[i]);
     }
@@ -753,16 +902,14 @@ __global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_zw(float2* __restrict__
 }
 
 // ---------------------------------------------------------------- packed kx = 0 / nx/2 plane
-// The packed slot holds Z = X0 + i XN where X0 and XN are the (complex) yz spectra of
-// the real x-axis planes kx = 0 and kx = nx/2.  Their folded weights and data terms are
-// stored as separate planes in [ky][kz] order so that a block reads contiguous runs.  Both are Hermitian in (ky, kz), so
-// X0(k) = (Z(k) + conj Z(-k))/2 and XN(k) = (Z(k) - conj Z(-k))/(2i).  One block
-// handles the column pair ky, -ky so that every partner is on chip.
+// The packed kx = 0 / kx = nx/2 plane where the fused z pass leaves it out: on 512-point z
+// axes, and on 256-point ones for the objective (mode 3).  One block handles the column pair ky, -ky so that every
+// partner is on chip.
 
 template <int L, bool OBJ>
 __global__ void __launch_bounds__(256) k_dc_nyquist(float2* __restrict__ S, int P, int ny,
-                                                    const float2* __restrict__ tw, const float* __restrict__ w0p,
-                                                    const float* __restrict__ wnyq, const float2* __restrict__ c0p,
+                                                    const float2* __restrict__ tw, const float* __restrict__ ws,
+                                                    const float2* __restrict__ cs, const float* __restrict__ wnyq,
                                                     const float2* __restrict__ cnyq, double* __restrict__ partials) {
   __shared__ float s_re[L * 2];
   __shared__ float s_im[L * 2];
@@ -795,9 +942,11 @@ __global__ void __launch_bounds__(256) k_dc_nyquist(float2* __restrict__ S, int 
     const int kz = q + T * i;
     if (kz < L) {
       const long long offn = (long long)myky * L + kz;
-      w0v[i] = w0p[offn];
+      const int WG = P < 16 ? P : 16;
+      const long long off0 = ((long long)myky * (P / WG) * L + kz) * WG;  // kx = 0 of the folded layout
+      w0v[i] = ws[off0];
       wnv[i] = wnyq[offn];
-      c0v[i] = c0p ? c0p[offn] : make_float2(0.f, 0.f);
+      c0v[i] = cs ? cs[off0] : make_float2(0.f, 0.f);
       cnv[i] = cnyq ? cnyq[offn] : make_float2(0.f, 0.f);
     }
   }
@@ -844,7 +993,7 @@ __global__ void __launch_bounds__(256) k_dc_nyquist(float2* __restrict__ S, int 
     for (int p = q; p < L; p += T) S[base + p * pstride] = make_float2(re[p * 2], im[p * 2]);
 }
 
-// Layout of the folded weight and data term (read only by the fused z pass): groups of
+// Layout of the folded weight and data term (read only by the z axis): groups of
 // WC_G = min(16, P) consecutive kx, each group contiguous along kz, i.e.
 // [ky][kx / WC_G][kz][kx % WC_G], so that a 16-column tile reads them as one contiguous
 // run along z instead of 64- and 128-byte pieces a plane apart.
@@ -856,9 +1005,9 @@ __device__ __forceinline__ long long wc_index(const Dims& d, int kz, int ky, int
 
 // ---------------------------------------------------------------- small maps: y, z passes in one launch
 // Where a (ky, kz) plane of the packed spectrum fits in LDS, one block per column kx does
-// for its plane what k_fft_cols<ny, 0>, k_fft_zw<nz, 2>, k_dc_nyquist and k_fft_cols<ny, 1>
+// for its plane what k_fft_cols<ny, 0>, k_fft_zw<nz, 2> and k_fft_cols<ny, 1>
 // do between them: the y then z forward transforms, the weight step (G = w~ Y - c; at kx = 0
-// the packed kx = 0 / nx/2 plane, split and rejoined as in k_dc_nyquist, its partners
+// the packed kx = 0 / nx/2 plane, split and rejoined as in k_fft_zw, its partners
 // (-ky, -kz) being in the same plane), and the z then y inverse transforms.  One launch
 // instead of four for maps whose iteration time is launch latency.  Plane in LDS [kz][ky].
 
@@ -881,8 +1030,7 @@ __device__ __forceinline__ void plane_pass(float* re, float* im, int ntr, int ts
 template <int NY, int NZ>
 __global__ void __launch_bounds__(256) k_yz_plane(Dims d, float2* __restrict__ S, const float2* __restrict__ twy,
                                                   const float2* __restrict__ twz, const float* __restrict__ ws,
-                                                  const float2* __restrict__ cs, const float* __restrict__ w0p,
-                                                  const float* __restrict__ wnyq, const float2* __restrict__ c0p,
+                                                  const float2* __restrict__ cs, const float* __restrict__ wnyq,
                                                   const float2* __restrict__ cnyq) {
   constexpr int NP = NY * NZ;
   __shared__ float s_re[NP];
@@ -928,9 +1076,9 @@ __global__ void __launch_bounds__(256) k_yz_plane(Dims d, float2* __restrict__ S
         const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
         const float2 B = make_float2(dd.y, -dd.x);
         const long long offn = (long long)ky * NZ + kz;
-        const float w0 = w0p[offn], wn = wnyq[offn];
-        const float2 c0 = c0p ? c0p[offn] : make_float2(0.f, 0.f);
-        const float2 cn = cnyq ? cnyq[offn] : make_float2(0.f, 0.f);
+        const long long o = wc_index(d, kz, ky, 0);
+        const float w0 = ws[o], wn = wnyq[offn];
+        const float2 c0 = cs[o], cn = cnyq[offn];
         const float2 g0 = make_float2(w0 * A.x - c0.x, w0 * A.y - c0.y);
         const float2 gn = make_float2(wn * B.x - cn.x, wn * B.y - cn.y);
         nv[i] = make_float2(g0.x - gn.y, g0.y + gn.x);
@@ -2128,9 +2276,8 @@ __device__ __forceinline__ int neg_mod(int k, int n) { return k == 0 ? 0 : n - k
 // Partial: max w~.
 
 __global__ void __launch_bounds__(256) k_fold(Dims d, const float* __restrict__ w, const float2* __restrict__ b,
-                                              float* __restrict__ ws, float* __restrict__ w0p,
-                                              float* __restrict__ wnyq, float2* __restrict__ cs,
-                                              float2* __restrict__ c0p, float2* __restrict__ cnyq,
+                                              float* __restrict__ ws, float* __restrict__ wnyq,
+                                              float2* __restrict__ cs, float2* __restrict__ cnyq,
                                               double* __restrict__ partials) {
   __shared__ double s_red[8];
   const int P = d.P;
@@ -2148,15 +2295,11 @@ __global__ void __launch_bounds__(256) k_fold(Dims d, const float* __restrict__ 
     const double ci = 0.5 * (wk * bk.y - wn * bn.y);
     const float wsv = (float)(wt * inv_n);
     const float2 csv = make_float2((float)(cr * inv_sqrt_n), (float)(ci * inv_sqrt_n));
-    const long long op = (long long)ky * d.nz + kz;  // [ky][kz] planes of kx = 0 and nx/2
+    const long long op = (long long)ky * d.nz + kz;  // [ky][kz] plane of kx = nx/2
     if (kx < P) {
       const long long o = wc_index(d, kz, ky, kx);
       ws[o] = wsv;
       cs[o] = csv;
-      if (kx == 0) {
-        w0p[op] = wsv;
-        c0p[op] = csv;
-      }
     } else {
       wnyq[op] = wsv;
       cnyq[op] = csv;
@@ -3018,11 +3161,9 @@ __global__ void __launch_bounds__(256) k_reduce(const double* __restrict__ parti
 }
 
 // The monitored objective F_eps(y_k) (eq 31 with eq 14) from fixed-order sums of the
-// partials: C0 + data partials of the z pass (pa) and of the kx = 0 / nx/2 plane (pb), plus
-// lam sum u|y| + mu sum v phi_eps + gamma sum (y - x_prev)^2 from the stencil kernel (pc:
+// partials: C0 + data partials of the z pass (pa), plus lam sum u|y| + mu sum v phi_eps + gamma sum (y - x_prev)^2 from the stencil kernel (pc:
 // three groups of nc).  One block; writes *out.
 __global__ void __launch_bounds__(256) k_obj_finish(const double* __restrict__ pa, int na,
-                                                    const double* __restrict__ pb, int nb,
                                                     const double* __restrict__ pc, int nc, double c0, double lam,
                                                     double mu, double gamma, double* __restrict__ out) {
   __shared__ double s_red[8];
@@ -3032,11 +3173,10 @@ __global__ void __launch_bounds__(256) k_obj_finish(const double* __restrict__ p
     return block_reduce<RED_OP_SUM>(acc, s_red);
   };
   const double A = sum(pa, na);
-  const double B = sum(pb, nb);
   const double L1 = sum(pc, nc);
   const double H = sum(pc + nc, nc);
   const double G = sum(pc + 2 * (long long)nc, nc);
-  if (threadIdx.x == 0) *out = c0 + A + B + lam * L1 + mu * H + gamma * G;
+  if (threadIdx.x == 0) *out = c0 + A + lam * L1 + mu * H + gamma * G;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -3089,31 +3229,33 @@ static int cu_count() {
 }
 
 // Fused z passes: one persistent block per resident slot (CUs x blocks per CU), rounded
-// down to a multiple of the 8 XCDs, or one block per tile when there are fewer tiles or
-// when persist is false (problems sharing the GPU with others).
+// down to a multiple of the 8 XCDs, or one block per tile when there are fewer tiles, when
+// persist is false (problems sharing the GPU with others) or when the packed plane rides.
 template <int L, int MODE, bool NTW>
-static hipError_t launch_zw(float2* S, int P, int ntiles, int total, long long pstride, long long bstride,
-                            const float2* tw, const float* ws, const float2* cs, double* partials, int NT, int T,
-                            bool persist, hipStream_t st, int* nblocks_out, int Pw, int kxo) {
+static hipError_t launch_zw(float2* S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
+                            const float2* tw, const FoldedData& fd, double* partials, int NT, int T, bool persist,
+                            hipStream_t st, int* nblocks_out, int Pw, int kxo) {
   int occ = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_fft_zw<L, MODE, NTW>, NT * T, 0) != hipSuccess || occ < 1)
     occ = 1;
   long long g = (long long)cu_count() * occ;
   if (g > 4096) g = 4096;  // the objective partials of mode 3 hold one value per block
-  if (g >= total || (!persist && MODE != 3)) g = total;
+  const int ride = ZPlane<L>::value == ZP_RIDE && MODE != 3 && kxo == 0 ? (ny / 2 + NT / 2) / (NT / 2) : 0;
+  if (g >= total || ((!persist || ride) && MODE != 3)) g = total;
   else if (g >= 8) g &= ~7LL;
   if (nblocks_out) *nblocks_out = (int)g;
-  k_fft_zw<L, MODE, NTW><<<dim3((unsigned)g), dim3(NT * T), 0, st>>>(S, P, ntiles, total, pstride, bstride, tw, ws, cs,
-                                                               partials, NT, Pw, kxo);
+  k_fft_zw<L, MODE, NTW><<<dim3((unsigned)(g + ride)), dim3(NT * T), 0, st>>>(S, P, ntiles, total, ny, pstride, bstride, tw,
+                                                                     fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials, NT, Pw,
+                                                                     kxo, ride);
   return hipGetLastError();
 }
 
-hipError_t launch_fft_cols(const Dims& d, float2* S, int axis, int mode, const float2* tw, const float* ws,
-                           const float2* cs, double* partials, hipStream_t st, int* nblocks_out, int nt,
-                           bool persist, int kx0, int nkx) {
+hipError_t launch_fft_cols(const Dims& d, float2* S, int axis, int mode, const float2* tw, const FoldedData* fdp,
+                           double* partials, hipStream_t st, int* nblocks_out, int nt, bool persist, int kx0,
+                           int nkx) {
   const int L = axis == 1 ? d.ny : d.nz;
   if (nt != 8 && nt != 16) return hipErrorInvalidValue;
-  if (mode < 0 || mode > 4 || (mode >= 2 && axis != 2)) return hipErrorInvalidValue;
+  if (mode < 0 || mode > 4 || (mode >= 2 && (axis != 2 || !fdp))) return hipErrorInvalidValue;
   if (nkx == 0) nkx = d.P - kx0;
   if (kx0 < 0 || nkx < 1 || kx0 + nkx > d.P || (kx0 > 0 && mode == 3)) return hipErrorInvalidValue;
   // the columns [kx0, kx0 + nkx): tiles over that range, strides of the full spectrum
@@ -3137,14 +3279,17 @@ hipError_t launch_fft_cols(const Dims& d, float2* S, int axis, int mode, const f
     }
     return hipGetLastError();
   }
+  // the fused z modes take whole tiles, of an even number of columns
+  if (Pc % NT != 0 || NT % 2 != 0) return hipErrorInvalidValue;
+  const FoldedData& fd = *fdp;
   // streaming weight loads where the folded weight and data term (6 bytes per voxel)
   // outgrow the 256 MiB last-level cache (measured at 512^3: 400 -> 391 us)
   const bool ntw = (double)d.nvox * 6.0 >= 256.0 * 1024 * 1024;
 #define SPG_ZW(MODE_) \
-  return launch_zw<L_, MODE_, false>(S, Pc, ntiles, total, pstride, bstride, tw, ws, cs, partials, NT, T, persist, \
+  return launch_zw<L_, MODE_, false>(S, Pc, ntiles, total, d.ny, pstride, bstride, tw, fd, partials, NT, T, persist, \
                                      st, nblocks_out, d.P, kx0)
 #define SPG_ZWN(MODE_) \
-  return launch_zw<L_, MODE_, true>(S, Pc, ntiles, total, pstride, bstride, tw, ws, cs, partials, NT, T, persist, \
+  return launch_zw<L_, MODE_, true>(S, Pc, ntiles, total, d.ny, pstride, bstride, tw, fd, partials, NT, T, persist, \
                                     st, nblocks_out, d.P, kx0)
   switch (mode) {
     case 2:
@@ -3167,13 +3312,12 @@ bool yz_plane_supported(const Dims& d) {
   return ok(d.ny) && ok(d.nz);
 }
 
-hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const float2* tw_z, const float* ws,
-                           const float2* cs, const float* w0p, const float* wnyq, const float2* c0p,
-                           const float2* cnyq, hipStream_t st) {
+hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const float2* tw_z, const FoldedData& fd,
+                           hipStream_t st) {
   if (!yz_plane_supported(d)) return hipErrorInvalidValue;
 #define SPG_YZ(NY_, NZ_)                                                                                      \
   if (d.ny == NY_ && d.nz == NZ_) {                                                                         \
-    k_yz_plane<NY_, NZ_><<<d.P, 256, 0, st>>>(d, S, tw_y, tw_z, ws, cs, w0p, wnyq, c0p, cnyq);                \
+    k_yz_plane<NY_, NZ_><<<d.P, 256, 0, st>>>(d, S, tw_y, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq);              \
     return hipGetLastError();                                                                               \
   }
 #define SPG_YZ4(NY_) SPG_YZ(NY_, 8) SPG_YZ(NY_, 16) SPG_YZ(NY_, 32) SPG_YZ(NY_, 64)
@@ -3183,18 +3327,19 @@ hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const f
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const float* w0p, const float* wnyq,
-                             const float2* c0p, const float2* cnyq, double* partials, hipStream_t st, int* nblocks_out) {
-  const int L = d.nz;
-  int T = 0;
-  SPG_DISPATCH_L(L, (T = DcT<L_>::T));
-  const dim3 grid(d.ny / 2 + 1), block(2 * T);
+bool dc_plane_apart(const Dims& d, bool obj) { return d.nz == 512 || (obj && d.nz == 256); }
+
+hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const FoldedData& fd, double* partials,
+                             hipStream_t st, int* nblocks_out) {
+  const dim3 grid(d.ny / 2 + 1);
   if (nblocks_out) *nblocks_out = d.ny / 2 + 1;
-  if (partials) {
-    SPG_DISPATCH_L(L, (k_dc_nyquist<L_, true><<<grid, block, 0, st>>>(S, d.P, d.ny, tw_z, w0p, wnyq, c0p, cnyq, partials)));
-  } else {
-    SPG_DISPATCH_L(L, (k_dc_nyquist<L_, false><<<grid, block, 0, st>>>(S, d.P, d.ny, tw_z, w0p, wnyq, c0p, cnyq, partials)));
-  }
+#define SPG_DC(L_, OBJ_)                                                                                       \
+  k_dc_nyquist<L_, OBJ_><<<grid, 2 * DcT<L_>::T, 0, st>>>(S, d.P, d.ny, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials)
+  if (d.nz == 512 && partials) SPG_DC(512, true);
+  else if (d.nz == 512) SPG_DC(512, false);
+  else if (d.nz == 256 && partials) SPG_DC(256, true);
+  else return hipErrorInvalidValue;
+#undef SPG_DC
   return hipGetLastError();
 }
 
@@ -3341,9 +3486,9 @@ hipError_t launch_fill(float* dst, long long n, float value, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_fold(const Dims& d, const float* w, const float2* b, float* ws, float* w0p, float* wnyq,
-                       float2* cs, float2* c0p, float2* cnyq, double* partials, int nblocks, hipStream_t st) {
-  k_fold<<<nblocks, 256, 0, st>>>(d, w, b, ws, w0p, wnyq, cs, c0p, cnyq, partials);
+hipError_t launch_fold(const Dims& d, const float* w, const float2* b, float* ws, float* wnyq, float2* cs,
+                       float2* cnyq, double* partials, int nblocks, hipStream_t st) {
+  k_fold<<<nblocks, 256, 0, st>>>(d, w, b, ws, wnyq, cs, cnyq, partials);
   return hipGetLastError();
 }
 
@@ -3373,9 +3518,9 @@ hipError_t launch_log_terms(const Dims& d, const float* hi, const uint16_t* lo, 
   return hipGetLastError();
 }
 
-hipError_t launch_obj_finish(const double* pa, int na, const double* pb, int nb, const double* pc, int nc, double c0,
-                             double lam, double mu, double gamma, double* out, hipStream_t st) {
-  k_obj_finish<<<1, 256, 0, st>>>(pa, na, pb, nb, pc, nc, c0, lam, mu, gamma, out);
+hipError_t launch_obj_finish(const double* pa, int na, const double* pc, int nc, double c0, double lam, double mu,
+                             double gamma, double* out, hipStream_t st) {
+  k_obj_finish<<<1, 256, 0, st>>>(pa, na, pc, nc, c0, lam, mu, gamma, out);
   return hipGetLastError();
 }
 
