@@ -309,12 +309,13 @@ spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, void* gout, bool
     for (int c = 0; c < nch; ++c) {
       const int kx0 = c * cw, nkx = nch > 1 ? cw : 0;
       prof_begin(P, SPG_KERNEL_FFT_Y_FWD);
-      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, twy, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx));
+      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, twy, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx,
+                                P->bf()));
       prof_end(P, SPG_KERNEL_FFT_Y_FWD);
       prof_begin(P, SPG_KERNEL_FFT_Z_WEIGHT);
       // the objective variant writes one partial per block: 16-column tiles keep <= 8192 blocks
       SPG_CK(P, launch_fft_cols(d, P->S(), 2, obj ? 3 : 2, twz, &fd, obj ? P->part() + kPartA : nullptr, st, nA,
-                                obj ? 16 : P->nt_z, !P->shared_gpu, kx0, nkx));
+                                obj ? 16 : P->nt_z, !P->shared_gpu, kx0, nkx, P->bf()));
       prof_end(P, SPG_KERNEL_FFT_Z_WEIGHT);
       if (c == 0 && dc_plane_apart(d, obj)) {  // the packed kx = 0 / nx/2 plane
         int nB = 0;
@@ -324,7 +325,8 @@ spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, void* gout, bool
         if (nA) *nA += nB;  // its partials follow the z pass's
       }
       prof_begin(P, SPG_KERNEL_FFT_Y_INV);
-      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, twy, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx));
+      SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, twy, nullptr, nullptr, st, nullptr, P->nt_y, true, kx0, nkx,
+                                P->bf()));
       prof_end(P, SPG_KERNEL_FFT_Y_INV);
     }
   }

@@ -84,7 +84,7 @@ struct FoldedData {
 hipError_t launch_fft_cols(const Dims& d, float2* S, int axis /*1 = y, 2 = z*/, int mode, const float2* tw,
                            const FoldedData* fd /* fused z modes */, double* partials, hipStream_t st,
                            int* nblocks_out, int nt = 16 /* columns per tile: 8 or 16 */, bool persist = true,
-                           int kx0 = 0, int nkx = 0);
+                           int kx0 = 0, int nkx = 0, bool bf16 = false /* bf16 storage */);
 // Small maps (ny, nz in {8, 16, 32, 64}): the y forward, z + weight + packed-plane and y inverse
 // passes in one launch, one block per (ky, kz) plane of a column kx.
 bool yz_plane_supported(const Dims& d);

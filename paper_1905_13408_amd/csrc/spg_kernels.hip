@@ -154,23 +154,41 @@ __device__ __forceinline__ void dft(float2* a) {
 // butterfly j reads j + r L/R, twiddles by exp(-+2 pi i r (j mod Ns) / (Ns R)), and
 // writes (j - j mod Ns) R + j mod Ns + r Ns.
 
-// Stage radices of a supported length L = 2^a 3^b 5^c (at most one 3 and one 5): for a
-// power of two, radix-8 stages and one closing radix-4 or radix-2 stage; for a mixed
-// length, the radix-5 / radix-3 stage first and then radix-4 stages (and one radix 2),
-// which keeps more threads per transform.  T (threads per transform) must divide L / R
-// of every stage; the default is the largest such value up to 16.
+// Stage radices of a supported length L: for a power of two, radix-8 stages and one closing
+// radix-4 or radix-2 stage, on T threads per transform, the largest divisor of every stage's
+// butterfly count up to 16.  80, 96, 160 and 192 have two plans:
+//   even: radix 8, then the radix-5 or radix-3 stage, then one closing radix 2, 4 or 8, on
+//   L / 8 threads of 8 points each, as many registers as the long powers of two need.  The
+//   first and last stage divide evenly among the threads; in the middle one, whose points
+//   pass through LDS on both sides, some threads have one butterfly fewer.
+//   wide: radix 5 or 3 first and radix 4 (and one radix 2) after it, on T threads as above
+//   (8 or 16 threads of 20 or 12 points: 354 registers in the 160-point z pass, one wave
+//   per SIMD).
+// Even against wide, us per pass at 160^3: z 19.7 and 26.0, y 8.7 + 10.2 and 11.5 + 12.8,
+// x 9.6 + 9.8 and 12.2 + 11.3.  The wide plan serves bf16 storage alone: it rounds the maps
+// next to the transforms to bf16, where a last-bit difference turns into whole bf16 steps
+// (1e-3 of single voxels after a reweight), so it keeps the arithmetic it had.
 struct RadixList {
   int n;
   int r[12];
 };
 
-constexpr RadixList make_plan(int L) {
+constexpr bool mixed_len(int L) { return (L & (L - 1)) != 0; }
+constexpr bool even_plan(int L, int T) { return mixed_len(L) && T == L / 8; }
+
+constexpr RadixList make_plan(int L, int T = 0) {
   RadixList p{};
   int rest = L;
+  if (even_plan(L, T)) {
+    const int odd = L % 5 == 0 ? 5 : 3;
+    p.r[p.n++] = 8;
+    p.r[p.n++] = odd;
+    p.r[p.n++] = L / (8 * odd);
+    return p;
+  }
   if (rest % 5 == 0) { p.r[p.n++] = 5; rest /= 5; }
   if (rest % 3 == 0) { p.r[p.n++] = 3; rest /= 3; }
-  const bool mixed = rest != L;
-  if (mixed) {
+  if (mixed_len(L)) {
     while (rest % 4 == 0 && rest > 2) { p.r[p.n++] = 4; rest /= 4; }
   } else {
     while (rest % 8 == 0) { p.r[p.n++] = 8; rest /= 8; }
@@ -198,7 +216,8 @@ constexpr int largest_divisor_le(int g, int cap) {
 template <int L>
 struct FftPlan {
   static constexpr RadixList plan = make_plan(L);
-  static constexpr int T = largest_divisor_le(plan_gcd(L), 16);
+  static constexpr int WIDE = largest_divisor_le(plan_gcd(L), 16);  // threads of the wide plan
+  static constexpr int T = mixed_len(L) ? L / 8 : WIDE;
 };
 
 // act = false: the thread takes part in the barriers only.
@@ -280,7 +299,7 @@ constexpr int reg_e(int L, int T) { return L / T; }
 
 template <int L, int TT = FftPlan<L>::T>
 struct RegPlan {
-  static constexpr RadixList plan = make_plan(L);
+  static constexpr RadixList plan = make_plan(L, TT);
   static constexpr int T = TT;
   static constexpr int E = L / T;
   static constexpr int ns = plan.n;
@@ -299,10 +318,11 @@ constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v / 2); }
 // apart for lanes in different butterfly groups, which would pile onto a few of the 32
 // banks; XOR-ing the lane's bits [log2 Ns, log2 Ns*R) with address bits above them (so
 // the map is a bijection on [0, L)) spreads 32 consecutive lanes over all banks, and the
-// next stage's contiguous reads only permute within aligned blocks.  Power-of-two L only.
+// next stage's contiguous reads only permute within aligned blocks.  On mixed lengths only
+// a first stage of radix 8 is swizzled, within its aligned blocks of 8.
 template <int L, int Ns, int R>
 __device__ __forceinline__ int swz(int e) {
-  if constexpr ((L & (L - 1)) != 0 || Ns >= 32) {
+  if constexpr (Ns >= 32 || (mixed_len(L) && R != 8)) {
     return e;
   } else {
     constexpr int ks = Ns * R > 32 ? ilog2c(Ns * R) : 5;
@@ -331,14 +351,16 @@ __device__ __forceinline__ void reg_stage(float2 (&a)[reg_e(L, TT)], float* __re
   constexpr int R = P::radix(S);
   constexpr int Ns = P::span(S);
   constexpr int T = P::T;
-  constexpr int NB = L / (R * T);
-  constexpr int STR = L / R;
+  constexpr int STR = L / R;  // butterflies
+  constexpr int NB = (STR + T - 1) / T;
   constexpr bool first = S == 0;
   constexpr bool last = S == P::ns - 1;
+  static_assert(STR % T == 0 || (!first && !last), "only a stage between LDS passes may be uneven");
   float2 v[NB][R];
   if (act) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
+      if (STR % T != 0 && q + T * b >= STR) break;
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         if constexpr (first) {
@@ -360,6 +382,7 @@ __device__ __forceinline__ void reg_stage(float2 (&a)[reg_e(L, TT)], float* __re
   for (int b = 0; b < NB; ++b) {
     if (!act) break;
     const int j = q + T * b;
+    if (STR % T != 0 && j >= STR) break;
     const int k = j % Ns;
     if constexpr (Ns > 1) {
 #pragma unroll
@@ -495,7 +518,7 @@ struct Row256 {
 // is one 1024-thread block per CU and an 8-column tile runs two blocks per CU.
 template <int L>
 struct ColT {
-  static constexpr int T = L == 512 ? 64 : ((L >= 256 && (L & (L - 1)) == 0) ? 32 : FftPlan<L>::T);
+  static constexpr int T = L == 512 ? 64 : (L == 256 ? 32 : FftPlan<L>::T);
 };
 
 // ---------------------------------------------------------------- XCD-aware block order
@@ -522,11 +545,13 @@ __device__ __forceinline__ double red_op(double a, double b) {
 // Reduce one value per thread over the block in a fixed order; result valid in thread 0.
 template <int OP>
 __device__ double block_reduce(double v, double* sh) {
-  // blockDim.x is a power of two or a multiple of 64
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nw = (blockDim.x + 63) >> 6;
-  const int width = blockDim.x < 64 ? (int)blockDim.x : 64;
-  for (int off = width >> 1; off > 0; off >>= 1) v = red_op<OP>(v, __shfl_xor(v, off, width));
+  const int width = min(64, (int)blockDim.x - 64 * wave);  // lanes of this wave
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(v, off);
+    if ((lane ^ off) < width) v = red_op<OP>(v, o);
+  }
   __syncthreads();
   if (lane == 0) sh[wave] = v;
   __syncthreads();
@@ -580,15 +605,14 @@ __device__ __forceinline__ void st_nt(V* __restrict__ base, unsigned boff, V v) 
     __builtin_nontemporal_store(__builtin_bit_cast(unsigned short, v), reinterpret_cast<unsigned short*>(p));
 }
 
-template <int L, int MODE>
-__global__ void __launch_bounds__(16 * ColT<L>::T) k_fft_cols(float2* __restrict__ S, int P, int ntiles,
+template <int L, int MODE, int T = ColT<L>::T>
+__global__ void __launch_bounds__(16 * T) k_fft_cols(float2* __restrict__ S, int P, int ntiles,
                                                               long long pstride, long long bstride,
                                                               const float2* __restrict__ tw, int NT) {
   static_assert(MODE == 0 || MODE == 1, "single transforms");
   __shared__ float s_re[L * 16];
   __shared__ float s_im[L * 16];
   __shared__ float2 s_tw[L];
-  constexpr int T = ColT<L>::T;
   constexpr int E = RegPlan<L, T>::E;
   const int tid = threadIdx.x;
   const int c = tid % NT, q = tid / NT;
@@ -702,8 +726,8 @@ __device__ __forceinline__ void dc_pairs(float2* __restrict__ S, int P, int ny, 
 }
 
 // ride: leading blocks of the launch that do the packed plane (ZP_RIDE).
-template <int L, int MODE, bool NTW = false>
-__global__ void __launch_bounds__(16 * ColT<L>::T)
+template <int L, int MODE, bool NTW = false, int T = ColT<L>::T>
+__global__ void __launch_bounds__(16 * T)
     k_fft_zw(float2* __restrict__ S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
              const float2* __restrict__ tw, const float* __restrict__ ws, const float2* __restrict__ cs,
              const float* __restrict__ wnyq, const float2* __restrict__ cnyq, double* __restrict__ partials, int NT, int Pw, int kxo, int ride) {
@@ -711,7 +735,6 @@ __global__ void __launch_bounds__(16 * ColT<L>::T)
   __shared__ float s_im[L * 16];
   __shared__ float2 s_tw[L];
   __shared__ double s_red[16];  // one slot per wave (up to 1024 threads)
-  constexpr int T = ColT<L>::T;
   constexpr int E = RegPlan<L, T>::E;
   const int tid = threadIdx.x;
   const int c = tid % NT, q = tid / NT;
@@ -1108,6 +1131,12 @@ __global__ void __launch_bounds__(256) k_yz_plane(Dims d, float2* __restrict__ S
 // the unnormalised inverse of the Hermitian row spectrum.
 // Block: NR rows; thread (row c = tid / T, q = tid % T); LDS row pitch M + 4.
 
+// Threads per row: bf16 maps keep the wide plan (see make_plan).
+template <int M, bool BF>
+struct RowT {
+  static constexpr int T = BF ? FftPlan<M>::WIDE : FftPlan<M>::T;
+};
+
 template <int M, bool BF>
 __global__ void __launch_bounds__(256) k_r2c_x(const void* __restrict__ rin, float2* __restrict__ S, int nrows,
                                                const float2* __restrict__ twm, const float2* __restrict__ twn,
@@ -1115,8 +1144,8 @@ __global__ void __launch_bounds__(256) k_r2c_x(const void* __restrict__ rin, flo
   __shared__ float s_re[(M + 4) * 16];  // row pitch = 4 (mod 8): two rows per 32 lanes
   __shared__ float s_im[(M + 4) * 16];
   __shared__ float2 s_tw[M];
-  constexpr int T = RegPlan<M>::T;
-  constexpr int E = RegPlan<M>::E;
+  constexpr int T = RowT<M, BF>::T;
+  constexpr int E = M / T;
   const int tid = threadIdx.x;
   const int c = tid / T, q = tid % T;
   const int row = blockIdx.x * NR + c;
@@ -1138,7 +1167,7 @@ __global__ void __launch_bounds__(256) k_r2c_x(const void* __restrict__ rin, flo
   __syncthreads();
   float* re = s_re + c * (M + 4);
   float* im = s_im + c * (M + 4);
-  fft_reg<M, false, RegPlan<M>::T, true>(a, re, im, 1, q, s_tw);
+  fft_reg<M, false, T, true>(a, re, im, 1, q, s_tw);
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < E; ++i) {
@@ -1174,8 +1203,8 @@ __global__ void __launch_bounds__(256) k_c2r_x(const float2* __restrict__ S, voi
   __shared__ float s_re[(M + 4) * 16];  // row pitch = 4 (mod 8): two rows per 32 lanes
   __shared__ float s_im[(M + 4) * 16];
   __shared__ float2 s_tw[M];
-  constexpr int T = RegPlan<M>::T;
-  constexpr int E = RegPlan<M>::E;
+  constexpr int T = RowT<M, BF>::T;
+  constexpr int E = M / T;
   const int tid = threadIdx.x;
   const int c = tid / T, q = tid % T;
   const int row = blockIdx.x * NR + c;
@@ -1213,7 +1242,7 @@ __global__ void __launch_bounds__(256) k_c2r_x(const float2* __restrict__ S, voi
     }
   }
   __syncthreads();
-  fft_reg<M, true, RegPlan<M>::T, true>(a, re, im, 1, q, s_tw);
+  fft_reg<M, true, T, true>(a, re, im, 1, q, s_tw);
   if (valid) {
     if constexpr (BF) {
       uint32_t* dst = reinterpret_cast<uint32_t*>(rout) + (long long)row * M;
@@ -1600,7 +1629,7 @@ constexpr int PP_KB = 2;  // planes per batch of the pipelined variant
 
 template <int M>
 struct PfT {  // threads per row of the M-point complex transforms
-  static constexpr int T = largest_divisor_le(plan_gcd(M), 32);
+  static constexpr int T = mixed_len(M) ? M / 8 : largest_divisor_le(plan_gcd(M), 32);
   static constexpr int E = M / T;
 };
 
@@ -3181,6 +3210,16 @@ __global__ void __launch_bounds__(256) k_obj_finish(const double* __restrict__ p
 
 // ---------------------------------------------------------------- launchers
 
+// The mixed lengths, on the wide plan's threads T_ (bf16 storage).
+#define SPG_DISPATCH_WIDE(Lv, CALL)                                                              \
+  switch (Lv) {                                                                                  \
+    case 80: { constexpr int L_ = 80, T_ = FftPlan<80>::WIDE; CALL; break; }                     \
+    case 96: { constexpr int L_ = 96, T_ = FftPlan<96>::WIDE; CALL; break; }                     \
+    case 160: { constexpr int L_ = 160, T_ = FftPlan<160>::WIDE; CALL; break; }                  \
+    case 192: { constexpr int L_ = 192, T_ = FftPlan<192>::WIDE; CALL; break; }                  \
+    default: return hipErrorInvalidValue;                                                        \
+  }
+
 #define SPG_DISPATCH_L(Lv, CALL)        \
   switch (Lv) {                         \
     case 2: { constexpr int L_ = 2; CALL; break; }     \
@@ -3199,27 +3238,6 @@ __global__ void __launch_bounds__(256) k_obj_finish(const double* __restrict__ p
     default: return hipErrorInvalidValue;              \
   }
 
-static int tpt(int L) {
-  int t = 0;
-  switch (L) {
-    case 2: t = FftPlan<2>::T; break;
-    case 4: t = FftPlan<4>::T; break;
-    case 8: t = FftPlan<8>::T; break;
-    case 16: t = FftPlan<16>::T; break;
-    case 32: t = FftPlan<32>::T; break;
-    case 64: t = FftPlan<64>::T; break;
-    case 128: t = FftPlan<128>::T; break;
-    case 256: t = FftPlan<256>::T; break;
-    case 512: t = FftPlan<512>::T; break;
-    case 80: t = FftPlan<80>::T; break;
-    case 96: t = FftPlan<96>::T; break;
-    case 160: t = FftPlan<160>::T; break;
-    case 192: t = FftPlan<192>::T; break;
-    default: t = 0;
-  }
-  return t;
-}
-
 static int cu_count() {
   int dev = 0, n = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -3231,12 +3249,12 @@ static int cu_count() {
 // Fused z passes: one persistent block per resident slot (CUs x blocks per CU), rounded
 // down to a multiple of the 8 XCDs, or one block per tile when there are fewer tiles, when
 // persist is false (problems sharing the GPU with others) or when the packed plane rides.
-template <int L, int MODE, bool NTW>
+template <int L, int MODE, bool NTW, int T = ColT<L>::T>
 static hipError_t launch_zw(float2* S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
-                            const float2* tw, const FoldedData& fd, double* partials, int NT, int T, bool persist,
+                            const float2* tw, const FoldedData& fd, double* partials, int NT, bool persist,
                             hipStream_t st, int* nblocks_out, int Pw, int kxo) {
   int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_fft_zw<L, MODE, NTW>, NT * T, 0) != hipSuccess || occ < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_fft_zw<L, MODE, NTW, T>, NT * T, 0) != hipSuccess || occ < 1)
     occ = 1;
   long long g = (long long)cu_count() * occ;
   if (g > 4096) g = 4096;  // the objective partials of mode 3 hold one value per block
@@ -3244,7 +3262,7 @@ static hipError_t launch_zw(float2* S, int P, int ntiles, int total, int ny, lon
   if (g >= total || ((!persist || ride) && MODE != 3)) g = total;
   else if (g >= 8) g &= ~7LL;
   if (nblocks_out) *nblocks_out = (int)g;
-  k_fft_zw<L, MODE, NTW><<<dim3((unsigned)(g + ride)), dim3(NT * T), 0, st>>>(S, P, ntiles, total, ny, pstride, bstride, tw,
+  k_fft_zw<L, MODE, NTW, T><<<dim3((unsigned)(g + ride)), dim3(NT * T), 0, st>>>(S, P, ntiles, total, ny, pstride, bstride, tw,
                                                                      fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials, NT, Pw,
                                                                      kxo, ride);
   return hipGetLastError();
@@ -3252,7 +3270,7 @@ static hipError_t launch_zw(float2* S, int P, int ntiles, int total, int ny, lon
 
 hipError_t launch_fft_cols(const Dims& d, float2* S, int axis, int mode, const float2* tw, const FoldedData* fdp,
                            double* partials, hipStream_t st, int* nblocks_out, int nt, bool persist, int kx0,
-                           int nkx) {
+                           int nkx, bool bf16) {
   const int L = axis == 1 ? d.ny : d.nz;
   if (nt != 8 && nt != 16) return hipErrorInvalidValue;
   if (mode < 0 || mode > 4 || (mode >= 2 && (axis != 2 || !fdp))) return hipErrorInvalidValue;
@@ -3266,13 +3284,22 @@ hipError_t launch_fft_cols(const Dims& d, float2* S, int axis, int mode, const f
   const int nbatch = axis == 1 ? d.nz : d.ny;
   const long long pstride = axis == 1 ? (long long)d.P : (long long)d.ny * d.P;
   const long long bstride = axis == 1 ? (long long)d.ny * d.P : (long long)d.P;
+  const bool wide = bf16 && mixed_len(L);
   int T = 0;
-  SPG_DISPATCH_L(L, (T = ColT<L_>::T));
+  if (wide) {
+    SPG_DISPATCH_WIDE(L, (T = T_));
+  } else {
+    SPG_DISPATCH_L(L, (T = ColT<L_>::T));
+  }
   const int total = ntiles * nbatch;
   if (mode < 2) {
     const dim3 grid(total), block(NT * T);
     if (nblocks_out) *nblocks_out = total;
-    if (mode == 0) {
+    if (wide && mode == 0) {
+      SPG_DISPATCH_WIDE(L, (k_fft_cols<L_, 0, T_><<<grid, block, 0, st>>>(S, Pc, ntiles, pstride, bstride, tw, NT)));
+    } else if (wide) {
+      SPG_DISPATCH_WIDE(L, (k_fft_cols<L_, 1, T_><<<grid, block, 0, st>>>(S, Pc, ntiles, pstride, bstride, tw, NT)));
+    } else if (mode == 0) {
       SPG_DISPATCH_L(L, (k_fft_cols<L_, 0><<<grid, block, 0, st>>>(S, Pc, ntiles, pstride, bstride, tw, NT)));
     } else {
       SPG_DISPATCH_L(L, (k_fft_cols<L_, 1><<<grid, block, 0, st>>>(S, Pc, ntiles, pstride, bstride, tw, NT)));
@@ -3285,25 +3312,31 @@ hipError_t launch_fft_cols(const Dims& d, float2* S, int axis, int mode, const f
   // streaming weight loads where the folded weight and data term (6 bytes per voxel)
   // outgrow the 256 MiB last-level cache (measured at 512^3: 400 -> 391 us)
   const bool ntw = (double)d.nvox * 6.0 >= 256.0 * 1024 * 1024;
-#define SPG_ZW(MODE_) \
-  return launch_zw<L_, MODE_, false>(S, Pc, ntiles, total, d.ny, pstride, bstride, tw, fd, partials, NT, T, persist, \
-                                     st, nblocks_out, d.P, kx0)
-#define SPG_ZWN(MODE_) \
-  return launch_zw<L_, MODE_, true>(S, Pc, ntiles, total, d.ny, pstride, bstride, tw, fd, partials, NT, T, persist, \
-                                    st, nblocks_out, d.P, kx0)
+#define SPG_ZW(MODE_, NTW_, ...)                                                                              \
+  return launch_zw<L_, MODE_, NTW_, ##__VA_ARGS__>(S, Pc, ntiles, total, d.ny, pstride, bstride, tw, fd, partials, NT, \
+                                                   persist, st, nblocks_out, d.P, kx0)
+  if (wide) {  // modes 2 and 3: bf16 storage has no reverse mode
+    if (mode == 2 && ntw) {
+      SPG_DISPATCH_WIDE(L, SPG_ZW(2, true, T_));
+    } else if (mode == 2) {
+      SPG_DISPATCH_WIDE(L, SPG_ZW(2, false, T_));
+    } else if (mode == 3) {
+      SPG_DISPATCH_WIDE(L, SPG_ZW(3, false, T_));
+    }
+    return hipErrorInvalidValue;
+  }
   switch (mode) {
     case 2:
       if (ntw) {
-        SPG_DISPATCH_L(L, SPG_ZWN(2));
+        SPG_DISPATCH_L(L, SPG_ZW(2, true));
       } else {
-        SPG_DISPATCH_L(L, SPG_ZW(2));
+        SPG_DISPATCH_L(L, SPG_ZW(2, false));
       }
       break;
-    case 3: SPG_DISPATCH_L(L, SPG_ZW(3)); break;
-    case 4: SPG_DISPATCH_L(L, SPG_ZW(4)); break;
+    case 3: SPG_DISPATCH_L(L, SPG_ZW(3, false)); break;
+    case 4: SPG_DISPATCH_L(L, SPG_ZW(4, false)); break;
   }
 #undef SPG_ZW
-#undef SPG_ZWN
   return hipErrorInvalidValue;
 }
 
@@ -3346,8 +3379,8 @@ hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const
 hipError_t launch_r2c_x(const Dims& d, const void* rin, bool rin_bf16, float2* S, const float2* tw_m,
                         const float2* tw_n, hipStream_t st) {
   const int M = d.P;
-  const int T = tpt(M);
-  if (T == 0) return hipErrorInvalidValue;
+  int T = 0;
+  SPG_DISPATCH_L(M, (T = rin_bf16 ? RowT<L_, true>::T : RowT<L_, false>::T));
   const int NR = 256 / T < 16 ? 256 / T : 16;
   const int nrows = d.ny * d.nz;
   const dim3 grid((nrows + NR - 1) / NR), block(NR * T);
@@ -3362,8 +3395,8 @@ hipError_t launch_r2c_x(const Dims& d, const void* rin, bool rin_bf16, float2* S
 hipError_t launch_c2r_x(const Dims& d, const float2* S, void* rout, bool rout_bf16, const float2* tw_m,
                         const float2* tw_n, hipStream_t st) {
   const int M = d.P;
-  const int T = tpt(M);
-  if (T == 0) return hipErrorInvalidValue;
+  int T = 0;
+  SPG_DISPATCH_L(M, (T = rout_bf16 ? RowT<L_, true>::T : RowT<L_, false>::T));
   const int NR = 256 / T < 16 ? 256 / T : 16;
   const int nrows = d.ny * d.nz;
   const dim3 grid((nrows + NR - 1) / NR), block(NR * T);
