@@ -1979,31 +1979,35 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
     }
   };
 
+  // ---- prologue of a slab: y on planes z0-1 and z0, whose words are requested together, and
+  // sc(z0); then the requests of the first step (plane z0+1, the outputs' inputs of plane z0),
+  // which the row transforms of the first batch hide.  (One memory latency before the
+  // transforms and none after, instead of two and one: 1 us of a slab.)
+  auto prologue = [&]() {
+    RawX ro[NO], rh;
+    double d1[NO], d2[NO];
+    float sc0[NO];
+    fetch_x(z0 - 1, ro, rh);
+    fetch_x(z0, rown, rhalo);
+    fetch_v(z0, rv);
+    store_plane(z0 - 1, ro, rh, d1, d2);
+    store_plane(z0, rown, rhalo, own_y, own_xk);
+    __syncthreads();  // twiddles and the y ring
+    compute_sc(z0, rv, sc0);
+    fetch_x(z0 + 1, rown, rhalo);
+    fetch_v(z0 + 1, rv);
+    fetch_out(z0, u_cur, xq_cur);
+  };
+
   for (int i = tid; i < M; i += blockDim.x) {
     s_tw[i] = twm[i];
     s_twn[i] = twn[i];
   }
   float2 sa[FE];
   if constexpr (!PIPE) {
-    // ---- prologue: the gradient rows of the first batch; y on planes z0-1, z0; sc(z0);
-    // prefetch plane z0+1, the outputs' inputs of plane z0 and the next batch's spectrum
     fetch_spec(z0, sa);
-    {
-      double d1[NO], d2[NO];
-      fetch_x(z0 - 1, rown, rhalo);
-      store_plane(z0 - 1, rown, rhalo, d1, d2);
-      fetch_x(z0, rown, rhalo);
-      fetch_v(z0, rv);
-      store_plane(z0, rown, rhalo, own_y, own_xk);
-    }
+    prologue();
     transform_phase(z0, z0, z0, sa);  // inverse half only; ends with a barrier
-    {
-      float sc0[NO];
-      compute_sc(z0, rv, sc0);
-    }
-    fetch_x(z0 + 1, rown, rhalo);
-    fetch_v(z0 + 1, rv);
-    fetch_out(z0, u_cur, xq_cur);
     fetch_spec(z0 + KB, sa);
 
     for (int zb = z0; zb < z1; zb += KB) {
@@ -2149,32 +2153,15 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
       }
     };
 
-    // ---- prologue: y on planes z0-1, z0; the first batch's gradient rows into slot 0;
-    // sc(z0); prefetch plane z0+1, the outputs' inputs of plane z0 and the spectrum of the
-    // second batch
+    // ---- the first batch's gradient rows into slot 0; the spectrum of the second batch
     fetch_spec(z0, sa);
-    {
-      double d1[NO], d2[NO];
-      fetch_x(z0 - 1, rown, rhalo);
-      store_plane(z0 - 1, rown, rhalo, d1, d2);
-      fetch_x(z0, rown, rhalo);
-      fetch_v(z0, rv);
-      store_plane(z0, rown, rhalo, own_y, own_xk);
-    }
-    __syncthreads();  // twiddles and the y rings
+    prologue();
     chunk1(z0, z0, 0, z0);
     wave_sync();
     chunk2(z0, z0, z0);
     wave_sync();
     chunk3(z0, z0, z0, 0);
     fetch_spec(z0 + KB, sa);
-    {
-      float sc0[NO];
-      compute_sc(z0, rv, sc0);
-    }
-    fetch_x(z0 + 1, rown, rhalo);
-    fetch_v(z0 + 1, rv);
-    fetch_out(z0, u_cur, xq_cur);
 
     int jb = 0;
     for (int zb = z0; zb < z1; zb += KB, ++jb) {
