@@ -156,6 +156,7 @@ struct spg_problem {
   // launch shapes (chosen by spg_autotune): columns per tile of the y and z passes, z-slab
   // depth of the stencil kernel
   int nt_y = 16, nt_z = 16, zc = PT_ZC;
+  int zc_own = 0;  // slab depth of a path that picks its own while no launch shape has been set (0: zc)
   bool fused = false;  // fused x-axis transforms in the stencil/prox kernel
   bool shared_gpu = false;  // being captured into a batch graph with other problems
   // unrolled solve recorded by spg_run_checkpointed for spg_vjp
@@ -426,7 +427,8 @@ spg_status spg_create(const spg_params* p, void* d_workspace, size_t bytes, void
   P->comp = (p->flags & SPG_FLAG_COMPENSATED) != 0;
   P->store = P->comp ? ST_COMP : ((p->flags & SPG_FLAG_BF16_STORAGE) ? ST_BF16 : ST_PLAIN);
   P->dn2 = dnorm2_of(p->nx, p->ny, p->nz);
-  P->fused = prox_fft_supported(P->d);
+  P->fused = prox_fft_runs(P->d, P->store);
+  if (P->fused && !prox_fft_supported(P->d)) P->zc_own = prox_fft_slab(P->d);
   // z-slab depth of the stencil kernel: 32 planes, or fewer on small maps, whose blocks
   // (ny / 4 tiles per slab) would otherwise be too few to keep more than a few CUs busy and
   // each march through many planes in turn
@@ -577,6 +579,7 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
     const double m_next = P->prm.accel ? (P->t - 1.0) / t_next : 0.0;
     const int nxt = 3 - P->cur - P->old;
     ProxArgs a = prox_args(P, nxt, P->m_cur, m_next);
+    if (fuse && P->zc_own) a.zc = P->zc_own;
     if (mon) {
       // 3 partials per block in region C (<= 3 x 65536; the slab depth does not change results)
       a.partials = P->part() + kPartC;
@@ -996,6 +999,7 @@ spg_status spg_set_launch_shape(spg_problem* P, int32_t nt_y, int32_t nt_z, int3
   P->nt_y = nt_y;
   P->nt_z = nt_z;
   P->zc = zc;
+  P->zc_own = 0;
   return SPG_OK;
 }
 
@@ -1004,13 +1008,13 @@ spg_status spg_set_fusion(spg_problem* P, int32_t enable) {
   if (s) return s;
   if (enable && !prox_fft_supported(P->d))
     return set_err(P, SPG_E_UNSUPPORTED, "fused x transforms need nx in {64, 128, 256, 512} and ny % 4 == 0");
-  P->fused = enable != 0;
+  if (prox_fft_supported(P->d)) P->fused = enable != 0;  // else the path is not the caller's to choose
   return SPG_OK;
 }
 
 spg_status spg_get_fusion(const spg_problem* P, int32_t* enabled) {
   if (!P || !enabled) return SPG_E_INVAL;
-  *enabled = P->fused ? 1 : 0;
+  *enabled = P->fused && prox_fft_supported(P->d) ? 1 : 0;
   return SPG_OK;
 }
 
@@ -1038,6 +1042,7 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
     std::vector<int> cand;
   };
   int fused = P->fused ? 1 : 0;
+  P->zc_own = 0;
   std::vector<Knob> knobs = {{&P->nt_y, {SPG_KERNEL_FFT_Y_FWD}, {16, 8}},
                              {&P->nt_z, {SPG_KERNEL_FFT_Z_WEIGHT}, {16, 8}}};
   if (P->fused) knobs.push_back({&fused, {SPG_KERNEL_PROX_TV, SPG_KERNEL_C2R_X, SPG_KERNEL_R2C_X}, {1, 0}});
@@ -1094,7 +1099,7 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
 // arguments: buffers, momenta, step, shapes, paths), and the part of it that advances.
 struct IterSig {
   spg_params prm;
-  int store, cur, old, nt_y, nt_z, zc;
+  int store, cur, old, nt_y, nt_z, zc, zc_own;
   bool prior_set, primed, unif_u, unif_v, fused;
   double lr, t, m_cur;
   int32_t j;
@@ -1108,6 +1113,7 @@ struct IterSig {
     g.nt_y = P->nt_y;
     g.nt_z = P->nt_z;
     g.zc = P->zc;
+    g.zc_own = P->zc_own;
     g.prior_set = P->prior_set;
     g.primed = P->primed;
     g.unif_u = P->unif_u;
@@ -1126,7 +1132,7 @@ struct IterSig {
     return a.nx == b.nx && a.ny == b.ny && a.nz == b.nz && a.lambda == b.lambda && a.mu == b.mu && a.eps == b.eps &&
            a.gamma == b.gamma && a.accel == b.accel && a.flags == b.flags && a.obj_every == b.obj_every &&
            hist_n == o.hist_n && store == o.store && cur == o.cur &&
-           old == o.old && nt_y == o.nt_y && nt_z == o.nt_z && zc == o.zc && prior_set == o.prior_set &&
+           old == o.old && nt_y == o.nt_y && nt_z == o.nt_z && zc == o.zc && zc_own == o.zc_own && prior_set == o.prior_set &&
            primed == o.primed && unif_u == o.unif_u && unif_v == o.unif_v && fused == o.fused && lr == o.lr &&
            t == o.t && m_cur == o.m_cur && j == o.j;
   }

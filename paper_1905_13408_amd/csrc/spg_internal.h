@@ -62,6 +62,9 @@ int prox_num_blocks(const Dims& d, int zc);
 // x-spectrum of y_{k+1} back into S.  Grids with nx in {32, 64, 128, 256, 512} and ny a
 // multiple of 4 (the kernel's tile height).
 bool prox_fft_supported(const Dims& d);
+// Whether the kernel takes this grid and storage: those, and nx = 160 but for bf16 storage.
+bool prox_fft_runs(const Dims& d, int store);
+int prox_fft_slab(const Dims& d);  // a slab depth for it
 int prox_fft_num_blocks(const Dims& d, int zc);
 // mon: also the per-block partials of the objective's penalty terms at y_k (3 x nblocks
 // into a.partials)

@@ -3433,11 +3433,28 @@ bool prox_fft_supported(const Dims& d) {
          d.ny % PF_TY == 0;
 }
 
+// 160 columns too, on the even plan's 10 threads per row, but not in bf16 storage, whose
+// rounded map buffer between the sweeps is part of its results.  Per iteration at 160^3: 86 us
+// against 95 with the separate sweeps, box 64 x 192 x 160 in fp32 47 against 58.  (192
+// columns: 141 against 120 -- six waves per block leave room for two blocks per CU only.)
+bool prox_fft_runs(const Dims& d, int store) {
+  return prox_fft_supported(d) || (d.nx == 160 && d.ny % PF_TY == 0 && (store == ST_PLAIN || store == ST_COMP));
+}
+
+// The most slabs that leave at most two blocks per CU at once, a third round of blocks being
+// as long as the first (160^3, 40 tiles: 10 to 12 slabs 86-94 us per iteration, 13 and more
+// 94-102, 8 and fewer 95 and up).
+int prox_fft_slab(const Dims& d) {
+  const int slabs = 512 / (d.ny / PF_TY) > 1 ? 512 / (d.ny / PF_TY) : 1;
+  const int zc = (d.nz + slabs - 1) / slabs;
+  return zc < 4 ? 4 : zc;
+}
+
 int prox_fft_num_blocks(const Dims& d, int zc) { return (d.ny / PF_TY) * ((d.nz + zc - 1) / zc); }
 
 hipError_t launch_prox_fft(const Dims& d, const ProxArgs& a, float2* S, const float2* tw_m, const float2* tw_n,
                            int store, hipStream_t st, bool mon) {
-  if (!prox_fft_supported(d) || a.zc < 1 || store < ST_PLAIN || store > ST_BF16) return hipErrorInvalidValue;
+  if (!prox_fft_runs(d, store) || a.zc < 1 || store < ST_PLAIN || store > ST_BF16) return hipErrorInvalidValue;
   const int nty = d.ny / PF_TY;
   const long long nblk = (long long)nty * ((d.nz + a.zc - 1) / a.zc);
   if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -3462,6 +3479,13 @@ hipError_t launch_prox_fft(const Dims& d, const ProxArgs& a, float2* S, const fl
     case 32: SPG_PF(32); break;
     case 64: SPG_PF(64); break;
     case 128: SPG_PF(128); break;
+    case 160:
+      if (store == ST_PLAIN) {
+        SPG_PF2(160, ST_PLAIN);
+      } else {
+        SPG_PF2(160, ST_COMP);
+      }
+      break;
     case 256: SPG_PF(256); break;
     default: SPG_PF(512); break;
   }

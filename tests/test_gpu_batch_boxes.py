@@ -12,12 +12,11 @@ from gpu_util import announce
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("sizes", [(160, 160, 192, 128)])
-def test_separate_path_members_equal_eager_runs(sizes):
+@pytest.mark.parametrize("shapes", [[(160, 160, 128), (192, 192, 192), (256, 160, 16), (128, 128, 128)]])
+def test_separate_path_members_equal_eager_runs(shapes):
     solvers, refs = [], []
-    for i, n in enumerate(sizes):
-        shape = (n, n, n)
-        rng = np.random.default_rng([5, i, n])
+    for i, shape in enumerate(shapes):
+        rng = np.random.default_rng([5, i, *shape])
         w = torch.from_numpy(synth.fourier_weights(shape).astype(np.float32)).cuda()
         b = torch.from_numpy((rng.standard_normal((*shape, 2), dtype=np.float32) * 0.3).view(np.complex64)[..., 0]).cuda()
         for lst in (solvers, refs):
@@ -25,7 +24,7 @@ def test_separate_path_members_equal_eager_runs(sizes):
             s.set_fusion(False)
             s.set_data(w, b)
             lst.append(s)
-    announce(f"batch of separate-path members {sizes} against eager runs")
+    announce(f"batch of separate-path members {shapes} against eager runs")
     batch = spg.SPGBatch(solvers)
     for r in refs:
         r.set_map(None)
