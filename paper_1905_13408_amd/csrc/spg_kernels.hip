@@ -1029,100 +1029,127 @@ __device__ __forceinline__ long long wc_index(const Dims& d, int kz, int ky, int
 }
 
 // ---------------------------------------------------------------- small maps: y, z passes in one launch
-// Where a (ky, kz) plane of the packed spectrum fits in LDS, one block per column kx does
+// Where a (ky, kz) plane of the packed spectrum fits in one block, one block per column kx does
 // for its plane what k_fft_cols<ny, 0>, k_fft_zw<nz, 2> and k_fft_cols<ny, 1>
 // do between them: the y then z forward transforms, the weight step (G = w~ Y - c; at kx = 0
 // the packed kx = 0 / nx/2 plane, split and rejoined as in k_fft_zw, its partners
 // (-ky, -kz) being in the same plane), and the z then y inverse transforms.  One launch
-// instead of four for maps whose iteration time is launch latency.  Plane in LDS [kz][ky].
+// instead of three for maps whose iteration time is latency.
+// 8 points per thread: a transform lies in at most 8 lanes of one wavefront, exchanges its
+// stages through its own LDS row (or column) without a block barrier, and only the turns from
+// rows to columns and back need one each.  Global loads and stores go straight to and from
+// the registers of the y transforms; the weights of the thread's column points are
+// requested at the start.  (Transforms held in LDS, a barrier on both sides of every stage
+// and 256 threads on any plane: 19.7 us per iteration at 32^3 and 42.3 at 64^3 against 16.9 and 29.1.)
 
-// The ntr transforms of L points at base t * tstride and point stride ps, G = 256 / T at a
-// time; every thread takes part in every barrier.
-template <int L, bool INV>
-__device__ __forceinline__ void plane_pass(float* re, float* im, int ntr, int tstride, int ps,
-                                           const float2* __restrict__ tw) {
-  constexpr int T = FftPlan<L>::T;
-  constexpr int G = 256 / T;
-  const int tid = threadIdx.x;
-  for (int c0 = 0; c0 < ntr; c0 += G) {
-    const int t = c0 + tid / T;
-    const bool act = t < ntr && tid < G * T;
-    const int off = act ? t * tstride : 0;
-    fft_lds<L, INV, T>(re + off, im + off, ps, tid % T, tw, act);
+// The stages of a transform of L points within one wavefront (see reg_stage).
+template <int L, int TT, int S, bool INV, bool SWZ>
+__device__ __forceinline__ void wave_stages(float2 (&a)[reg_e(L, TT)], float* re, float* im, int ps, int q,
+                                            const float2* twl) {
+  if constexpr (S < RegPlan<L, TT>::ns) {
+    reg_stage<L, TT, S, INV, SWZ, true>(a, re, im, ps, q, twl);
+    wave_stages<L, TT, S + 1, INV, SWZ>(a, re, im, ps, q, twl);
   }
 }
 
 template <int NY, int NZ>
-__global__ void __launch_bounds__(256) k_yz_plane(Dims d, float2* __restrict__ S, const float2* __restrict__ twy,
-                                                  const float2* __restrict__ twz, const float* __restrict__ ws,
-                                                  const float2* __restrict__ cs, const float* __restrict__ wnyq,
-                                                  const float2* __restrict__ cnyq) {
-  constexpr int NP = NY * NZ;
-  __shared__ float s_re[NP];
-  __shared__ float s_im[NP];
+__global__ void __launch_bounds__(NY * NZ / 8) k_yz_plane(Dims d, float2* __restrict__ S,
+                                                          const float2* __restrict__ twy,
+                                                          const float2* __restrict__ twz,
+                                                          const float* __restrict__ ws, const float2* __restrict__ cs,
+                                                          const float* __restrict__ wnyq,
+                                                          const float2* __restrict__ cnyq) {
+  constexpr int E = 8, TY = NY / E, TZ = NZ / E;
+  constexpr int PY = NY + 1;  // row pitch: a column's points lie in different banks
+  __shared__ float s_re[NZ * PY];
+  __shared__ float s_im[NZ * PY];
   __shared__ float2 s_twy[NY];
   __shared__ float2 s_twz[NZ];
   const int tid = threadIdx.x;
   const int kx = blockIdx.x;
   const int P = d.P;
-  float2* __restrict__ Sc = S + kx;
-  for (int i = tid; i < NY; i += 256) s_twy[i] = twy[i];
-  for (int i = tid; i < NZ; i += 256) s_twz[i] = twz[i];
-  for (int e = tid; e < NP; e += 256) {
-    const float2 v = Sc[(long long)e * P];  // (kz NY + ky) P + kx
-    s_re[e] = v.x;
-    s_im[e] = v.y;
+  const int row = tid / TY, qy = tid % TY;  // y transforms: row kz = row, points ky = qy + TY i
+  const int col = tid / TZ, qz = tid % TZ;  // z transforms: column ky = col, points kz = qz + TZ i
+  float2* __restrict__ Sr = S + ((long long)row * NY + qy) * P + kx;
+  float2 a[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) a[i] = Sr[(long long)(TY * i) * P];
+  float wv[E], wn[E];
+  float2 cv[E], cn[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const long long o = wc_index(d, qz + TZ * i, col, kx);
+    wv[i] = ws[o];
+    cv[i] = cs[o];
+    if (kx == 0) {
+      const long long on = (long long)col * NZ + qz + TZ * i;
+      wn[i] = wnyq[on];
+      cn[i] = cnyq[on];
+    }
   }
-  plane_pass<NY, false>(s_re, s_im, NZ, NY, 1, s_twy);
-  plane_pass<NZ, false>(s_re, s_im, NY, 1, NY, s_twz);
+  for (int i = tid; i < NY; i += NY * NZ / 8) s_twy[i] = twy[i];
+  for (int i = tid; i < NZ; i += NY * NZ / 8) s_twz[i] = twz[i];
   __syncthreads();
+  float* rre = s_re + row * PY;
+  float* rim = s_im + row * PY;
+  wave_stages<NY, TY, 0, false, true>(a, rre, rim, 1, qy, s_twy);
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    rre[qy + TY * i] = a[i].x;
+    rim[qy + TY * i] = a[i].y;
+  }
+  __syncthreads();
+  float* cre = s_re + col;
+  float* cim = s_im + col;
+#pragma unroll
+  for (int i = 0; i < E; ++i) a[i] = make_float2(cre[(qz + TZ * i) * PY], cim[(qz + TZ * i) * PY]);
+  wave_sync();
+  wave_stages<NZ, TZ, 0, false, false>(a, cre, cim, PY, qz, s_twz);
   if (kx > 0) {
-    for (int e = tid; e < NP; e += 256) {
-      const int kz = e / NY, ky = e % NY;
-      const long long o = wc_index(d, kz, ky, kx);
-      const float wv = ws[o];
-      const float2 cv = cs[o];
-      const float yr = s_re[e], yi = s_im[e];
-      s_re[e] = wv * yr - cv.x;
-      s_im[e] = wv * yi - cv.y;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const float yr = a[i].x, yi = a[i].y;
+      a[i] = make_float2(wv[i] * yr - cv[i].x, wv[i] * yi - cv[i].y);
     }
   } else {
-    constexpr int EP = (NP + 255) / 256;
-    float2 nv[EP];
+    wave_sync();
 #pragma unroll
-    for (int i = 0; i < EP; ++i) {
-      const int e = tid + 256 * i;
-      if (e < NP) {
-        const int kz = e / NY, ky = e % NY;
-        const int ep = ((NZ - kz) % NZ) * NY + (NY - ky) % NY;
-        const float2 z1 = make_float2(s_re[e], s_im[e]);
-        const float2 z2 = make_float2(s_re[ep], s_im[ep]);
-        const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
-        const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
-        const float2 B = make_float2(dd.y, -dd.x);
-        const long long offn = (long long)ky * NZ + kz;
-        const long long o = wc_index(d, kz, ky, 0);
-        const float w0 = ws[o], wn = wnyq[offn];
-        const float2 c0 = cs[o], cn = cnyq[offn];
-        const float2 g0 = make_float2(w0 * A.x - c0.x, w0 * A.y - c0.y);
-        const float2 gn = make_float2(wn * B.x - cn.x, wn * B.y - cn.y);
-        nv[i] = make_float2(g0.x - gn.y, g0.y + gn.x);
-      }
+    for (int i = 0; i < E; ++i) {
+      cre[(qz + TZ * i) * PY] = a[i].x;
+      cim[(qz + TZ * i) * PY] = a[i].y;
     }
     __syncthreads();
+    const int colp = col == 0 ? 0 : NY - col;
 #pragma unroll
-    for (int i = 0; i < EP; ++i) {
-      const int e = tid + 256 * i;
-      if (e < NP) {
-        s_re[e] = nv[i].x;
-        s_im[e] = nv[i].y;
-      }
+    for (int i = 0; i < E; ++i) {
+      const int kz = qz + TZ * i, kzp = kz == 0 ? 0 : NZ - kz;
+      const float2 z1 = a[i];
+      const float2 z2 = make_float2(s_re[kzp * PY + colp], s_im[kzp * PY + colp]);
+      const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
+      const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
+      const float2 B = make_float2(dd.y, -dd.x);
+      const float2 g0 = make_float2(wv[i] * A.x - cv[i].x, wv[i] * A.y - cv[i].y);
+      const float2 gn = make_float2(wn[i] * B.x - cn[i].x, wn[i] * B.y - cn[i].y);
+      a[i] = make_float2(g0.x - gn.y, g0.y + gn.x);
     }
+    __syncthreads();  // every partner read
   }
-  plane_pass<NZ, true>(s_re, s_im, NY, 1, NY, s_twz);
-  plane_pass<NY, true>(s_re, s_im, NZ, NY, 1, s_twy);
+  wave_sync();
+  wave_stages<NZ, TZ, 0, true, false>(a, cre, cim, PY, qz, s_twz);
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    cre[(qz + TZ * i) * PY] = a[i].x;
+    cim[(qz + TZ * i) * PY] = a[i].y;
+  }
   __syncthreads();
-  for (int e = tid; e < NP; e += 256) Sc[(long long)e * P] = make_float2(s_re[e], s_im[e]);
+#pragma unroll
+  for (int i = 0; i < E; ++i) a[i] = make_float2(rre[qy + TY * i], rim[qy + TY * i]);
+  wave_sync();
+  wave_stages<NY, TY, 0, true, true>(a, rre, rim, 1, qy, s_twy);
+#pragma unroll
+  for (int i = 0; i < E; ++i) Sr[(long long)(TY * i) * P] = a[i];
 }
 
 // ---------------------------------------------------------------- x-axis real FFTs
@@ -3339,7 +3366,7 @@ hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const f
   if (!yz_plane_supported(d)) return hipErrorInvalidValue;
 #define SPG_YZ(NY_, NZ_)                                                                                      \
   if (d.ny == NY_ && d.nz == NZ_) {                                                                         \
-    k_yz_plane<NY_, NZ_><<<d.P, 256, 0, st>>>(d, S, tw_y, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq);              \
+    k_yz_plane<NY_, NZ_><<<d.P, NY_ * NZ_ / 8, 0, st>>>(d, S, tw_y, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq);              \
     return hipGetLastError();                                                                               \
   }
 #define SPG_YZ4(NY_) SPG_YZ(NY_, 8) SPG_YZ(NY_, 16) SPG_YZ(NY_, 32) SPG_YZ(NY_, 64)
