@@ -339,7 +339,7 @@ typedef enum {
   SPG_KERNEL_FFT_Y_FWD = 0, /* y-axis forward column FFT                               */
   SPG_KERNEL_FFT_Z_WEIGHT,  /* z-axis forward FFT, Fourier weight multiply, inverse FFT  */
   SPG_KERNEL_DC_NYQUIST,    /* the packed kx = 0 / kx = nx/2 plane where it is launched  */
-                            /* apart from the z pass (nz = 512; checks at nz = 256)      */
+                            /* apart from the z pass (nz = 512)                          */
   SPG_KERNEL_FFT_Y_INV,     /* y-axis inverse column FFT                               */
   SPG_KERNEL_C2R_X,         /* x-axis inverse real FFT of the gradient spectrum         */
   SPG_KERNEL_PROX_TV,       /* smoothed-TV stencil, gradient step, soft threshold, momentum */

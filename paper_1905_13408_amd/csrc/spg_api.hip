@@ -318,7 +318,7 @@ spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, void* gout, bool
       SPG_CK(P, launch_fft_cols(d, P->S(), 2, obj ? 3 : 2, twz, &fd, obj ? P->part() + kPartA : nullptr, st, nA,
                                 obj ? 16 : P->nt_z, !P->shared_gpu, kx0, nkx, P->bf()));
       prof_end(P, SPG_KERNEL_FFT_Z_WEIGHT);
-      if (c == 0 && dc_plane_apart(d, obj)) {  // the packed kx = 0 / nx/2 plane
+      if (c == 0 && dc_plane_apart(d)) {  // the packed kx = 0 / nx/2 plane
         int nB = 0;
         prof_begin(P, SPG_KERNEL_DC_NYQUIST);
         SPG_CK(P, launch_dc_nyquist(d, P->S(), twz, fd, obj ? P->part() + kPartA + *nA : nullptr, st, &nB));
@@ -1399,7 +1399,7 @@ spg_status hessian_data(spg_problem* P, const float* in, float* out) {
   FoldedData fd = folded(P);
   fd.cs = fd.cnyq = nullptr;
   SPG_CK(P, launch_fft_cols(d, P->S(), 2, 4, P->at<float2>(P->lay.tw_z), &fd, nullptr, st, nullptr));
-  if (dc_plane_apart(d, false))
+  if (dc_plane_apart(d))
     SPG_CK(P, launch_dc_nyquist(d, P->S(), P->at<float2>(P->lay.tw_z), fd, nullptr, st, nullptr));
   SPG_CK(P, launch_fft_cols(d, P->S(), 1, 1, P->at<float2>(P->lay.tw_y), nullptr, nullptr, st, nullptr));
   SPG_CK(P, launch_c2r_x(d, P->S(), out, false, P->at<float2>(P->lay.tw_m), P->at<float2>(P->lay.tw_n), st));

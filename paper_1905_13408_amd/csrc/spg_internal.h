@@ -93,9 +93,8 @@ hipError_t launch_fft_cols(const Dims& d, float2* S, int axis /*1 = y, 2 = z*/, 
 bool yz_plane_supported(const Dims& d);
 hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const float2* tw_z, const FoldedData& fd,
                            hipStream_t st);
-// Whether the packed plane is left out of the fused z modes (obj: of mode 3) and has a launch
-// of its own.
-bool dc_plane_apart(const Dims& d, bool obj);
+// Whether the packed plane is left out of the fused z modes and has a launch of its own.
+bool dc_plane_apart(const Dims& d);
 hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const FoldedData& fd, double* partials,
                              hipStream_t st, int* nblocks_out);
 hipError_t launch_r2c_x(const Dims& d, const void* rin, bool rin_bf16, float2* S, const float2* tw_m,

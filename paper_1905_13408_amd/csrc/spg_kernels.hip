@@ -654,16 +654,19 @@ __global__ void __launch_bounds__(16 * T) k_fft_cols(float2* __restrict__ S, int
 // rows ky and -ky would have are therefore cut the other way: one takes the first H = NT/2
 // columns of both rows, the other the last H (rows 0 and ny/2, their own partners, form one
 // pair): same work per unit and no launch of its own for the plane (ZP_PAIR).
-// That takes registers, so on axes of 256 points, whose blocks have none to spare, whole
-// column pairs run as the first blocks of the launch instead (ZP_RIDE, dc_pairs), one block
-// per tile in place of persistent blocks; on 512-point axes, where they would run as a second
-// round behind one persistent block per CU, the plane has its own launch (ZP_APART,
-// k_dc_nyquist, 14.5 us of 1560 per iteration).  z pass with the plane, apart / riding /
-// paired: 128^3 20.5 / 16.4 / 11.0 us, 256^3 55 / 44.5 / 60 us, 512^3 385 / - / 434 us.
+// That takes registers, so on axes of 256 points, whose blocks have none to spare where
+// several share a CU, whole column pairs run as the first blocks of the launch instead
+// (ZP_RIDE, dc_pairs), one block per tile in place of persistent blocks; on 512-point axes,
+// where they would run as a second round behind one persistent block per CU, the plane has its
+// own launch (ZP_APART, k_dc_nyquist, 14.5 us of 1560 per iteration).  z pass with the plane,
+// apart / riding / paired: 128^3 20.5 / 16.4 / 11.0 us, 256^3 55 / 44.5 / 60 us, 256 x 32 x 64
+// (64 tiles) 16.2 / 19.2 / 8.5 us, 512^3 385 / - / 434 us.
 enum { ZP_PAIR, ZP_RIDE, ZP_APART };
-template <int L>
+// the way of a pass with more tiles than CUs; with fewer, and for the objective, 256-point
+// passes are paired too
+template <int L, int MODE>
 struct ZPlane {
-  static constexpr int value = L < 256 ? ZP_PAIR : (L == 256 ? ZP_RIDE : ZP_APART);
+  static constexpr int value = L < 256 || (L == 256 && MODE == 3) ? ZP_PAIR : (L == 256 ? ZP_RIDE : ZP_APART);
 };
 
 // ZP_RIDE: thread (c, q) holds column c & 1 of the block's pair c / 2, points q + T i.
@@ -728,11 +731,12 @@ __device__ __forceinline__ void dc_pairs(float2* __restrict__ S, int P, int ny, 
 // ride: leading blocks of the launch that do the packed plane (ZP_RIDE).  160- and 192-point
 // passes are held to four waves per SIMD, 128 registers instead of 135 (3 to 7% of an
 // iteration on boxes of 160 and 192 planes).
-template <int L, int MODE, bool NTW = false, int T = ColT<L>::T>
+template <int L, int MODE, bool NTW = false, int T = ColT<L>::T, int ZP = ZPlane<L, MODE>::value>
 __global__ void __launch_bounds__(16 * T, even_plan(L, T) ? 4 : 1)
     k_fft_zw(float2* __restrict__ S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
              const float2* __restrict__ tw, const float* __restrict__ ws, const float2* __restrict__ cs,
-             const float* __restrict__ wnyq, const float2* __restrict__ cnyq, double* __restrict__ partials, int NT, int Pw, int kxo, int ride) {
+             const float* __restrict__ wnyq, const float2* __restrict__ cnyq, double* __restrict__ partials, int NT,
+             int Pw, int kxo, int ride) {
   __shared__ float s_re[L * 16];
   __shared__ float s_im[L * 16];
   __shared__ float2 s_tw[L];
@@ -741,8 +745,8 @@ __global__ void __launch_bounds__(16 * T, even_plan(L, T) ? 4 : 1)
   const int tid = threadIdx.x;
   const int c = tid % NT, q = tid / NT;
   static_assert(MODE >= 2 && MODE <= 4, "fused z modes");
-  constexpr bool PAIR = ZPlane<L>::value == ZP_PAIR;
-  if constexpr (ZPlane<L>::value == ZP_RIDE && MODE != 3) {
+  constexpr bool PAIR = ZP == ZP_PAIR;
+  if constexpr (ZP == ZP_RIDE) {
     if ((int)blockIdx.x < ride) {
       dc_pairs<L, MODE != 4>(S, Pw, ny, pstride, tw, ws, cs, wnyq, cnyq, s_re, s_im, s_tw, NT, c, q);
       return;
@@ -927,8 +931,8 @@ __global__ void __launch_bounds__(16 * T, even_plan(L, T) ? 4 : 1)
 }
 
 // ---------------------------------------------------------------- packed kx = 0 / nx/2 plane
-// The packed kx = 0 / kx = nx/2 plane where the fused z pass leaves it out: on 512-point z
-// axes, and on 256-point ones for the objective (mode 3).  One block handles the column pair ky, -ky so that every
+// The packed kx = 0 / kx = nx/2 plane where the fused z pass leaves it out, on 512-point z
+// axes.  One block handles the column pair ky, -ky so that every
 // partner is on chip.
 
 template <int L, bool OBJ>
@@ -3265,22 +3269,28 @@ static int cu_count() {
 // Fused z passes: one persistent block per resident slot (CUs x blocks per CU), rounded
 // down to a multiple of the 8 XCDs, or one block per tile when there are fewer tiles, when
 // persist is false (problems sharing the GPU with others) or when the packed plane rides.
-template <int L, int MODE, bool NTW, int T = ColT<L>::T>
+template <int L, int MODE, bool NTW, int T = ColT<L>::T, int ZP = ZPlane<L, MODE>::value>
 static hipError_t launch_zw(float2* S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
                             const float2* tw, const FoldedData& fd, double* partials, int NT, bool persist,
                             hipStream_t st, int* nblocks_out, int Pw, int kxo) {
+  const int cus = cu_count();
+  if constexpr (ZP == ZP_RIDE) {
+    if (total <= cus)
+      return launch_zw<L, MODE, NTW, T, ZP_PAIR>(S, P, ntiles, total, ny, pstride, bstride, tw, fd, partials, NT,
+                                                 persist, st, nblocks_out, Pw, kxo);
+  }
   int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_fft_zw<L, MODE, NTW, T>, NT * T, 0) != hipSuccess || occ < 1)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_fft_zw<L, MODE, NTW, T, ZP>, NT * T, 0) != hipSuccess ||
+      occ < 1)
     occ = 1;
-  long long g = (long long)cu_count() * occ;
+  long long g = (long long)cus * occ;
   if (g > 4096) g = 4096;  // the objective partials of mode 3 hold one value per block
-  const int ride = ZPlane<L>::value == ZP_RIDE && MODE != 3 && kxo == 0 ? (ny / 2 + NT / 2) / (NT / 2) : 0;
+  const int ride = ZP == ZP_RIDE && kxo == 0 ? (ny / 2 + NT / 2) / (NT / 2) : 0;
   if (g >= total || ((!persist || ride) && MODE != 3)) g = total;
   else if (g >= 8) g &= ~7LL;
   if (nblocks_out) *nblocks_out = (int)g;
-  k_fft_zw<L, MODE, NTW, T><<<dim3((unsigned)(g + ride)), dim3(NT * T), 0, st>>>(S, P, ntiles, total, ny, pstride, bstride, tw,
-                                                                     fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials, NT, Pw,
-                                                                     kxo, ride);
+  k_fft_zw<L, MODE, NTW, T, ZP><<<dim3((unsigned)(g + ride)), dim3(NT * T), 0, st>>>(
+      S, P, ntiles, total, ny, pstride, bstride, tw, fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials, NT, Pw, kxo, ride);
   return hipGetLastError();
 }
 
@@ -3376,19 +3386,18 @@ hipError_t launch_yz_plane(const Dims& d, float2* S, const float2* tw_y, const f
   return hipErrorInvalidValue;
 }
 
-bool dc_plane_apart(const Dims& d, bool obj) { return d.nz == 512 || (obj && d.nz == 256); }
+bool dc_plane_apart(const Dims& d) { return d.nz == 512; }
 
 hipError_t launch_dc_nyquist(const Dims& d, float2* S, const float2* tw_z, const FoldedData& fd, double* partials,
                              hipStream_t st, int* nblocks_out) {
-  const dim3 grid(d.ny / 2 + 1);
+  if (!dc_plane_apart(d)) return hipErrorInvalidValue;
+  constexpr int L = 512;
+  const dim3 grid(d.ny / 2 + 1), block(2 * DcT<L>::T);
   if (nblocks_out) *nblocks_out = d.ny / 2 + 1;
-#define SPG_DC(L_, OBJ_)                                                                                       \
-  k_dc_nyquist<L_, OBJ_><<<grid, 2 * DcT<L_>::T, 0, st>>>(S, d.P, d.ny, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials)
-  if (d.nz == 512 && partials) SPG_DC(512, true);
-  else if (d.nz == 512) SPG_DC(512, false);
-  else if (d.nz == 256 && partials) SPG_DC(256, true);
-  else return hipErrorInvalidValue;
-#undef SPG_DC
+  if (partials)
+    k_dc_nyquist<L, true><<<grid, block, 0, st>>>(S, d.P, d.ny, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials);
+  else
+    k_dc_nyquist<L, false><<<grid, block, 0, st>>>(S, d.P, d.ny, tw_z, fd.ws, fd.cs, fd.wnyq, fd.cnyq, partials);
   return hipGetLastError();
 }
 
