@@ -349,6 +349,7 @@ spg_status r2c(spg_problem* P, const void* rin, bool rin_bf16) {
 ProxArgs prox_args(spg_problem* P, int nxt, double m, double m_next) {
   ProxArgs a{};
   a.rbuf = P->rbuf();
+  a.gsrc = P->rbuf();
   a.xk_hi = P->xhi(P->cur);
   a.xk_lo = P->xlo(P->cur);
   a.xo_hi = P->xhi(P->old);
@@ -556,7 +557,7 @@ spg_status spg_set_map(spg_problem* P, const float* d_x0) {
   return SPG_OK;
 }
 
-// One SPG iteration; with capture_g, the data gradient of y_k is also copied there (fp32).
+// One SPG iteration; with capture_g, the data gradient of y_k is left there (fp32).
 static spg_status iterate_once(spg_problem* P, float* capture_g) {
   spg_status s;
   const Dims& d = P->d;
@@ -572,14 +573,13 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
     // and the stencil kernel of this iteration
     const bool mon = P->mon_every > 0 && !capture_g && P->j % P->mon_every == 0;
     int nA = 0, nC = 0;
-    if ((s = gradient_pipeline(P, mon, &nA, P->rbuf(), P->bf(), !fuse))) return s;
-    if (capture_g)
-      SPG_CK(P, hipMemcpyAsync(capture_g, P->rbuf(), (size_t)d.nvox * 4, hipMemcpyDeviceToDevice, P->stream));
+    if ((s = gradient_pipeline(P, mon, &nA, capture_g ? capture_g : P->rbuf(), P->bf(), !fuse))) return s;
     const double t_next = P->prm.accel ? 0.5 * (1.0 + std::sqrt(1.0 + 4.0 * P->t * P->t)) : 1.0;
     const double m_next = P->prm.accel ? (P->t - 1.0) / t_next : 0.0;
     const int nxt = 3 - P->cur - P->old;
     ProxArgs a = prox_args(P, nxt, P->m_cur, m_next);
     if (fuse && P->zc_own) a.zc = P->zc_own;
+    if (capture_g) a.gsrc = capture_g;
     if (mon) {
       // 3 partials per block in region C (<= 3 x 65536; the slab depth does not change results)
       a.partials = P->part() + kPartC;
@@ -1318,7 +1318,7 @@ spg_status spg_batch_run(spg_batch* B, int32_t K) {
 
 namespace {
 struct VjpLayout {
-  size_t ck, ck_slot, seg_x, seg_g, abar, zbar, hz, rbar, part, res, total;
+  size_t ck, ck_slot, seg_x, seg_g, abar, zbar, hz, rbar, total;
   int nseg;
 };
 
@@ -1343,10 +1343,6 @@ VjpLayout vjp_layout(const spg_problem* P, int K, int C) {
   off += n4;
   L.rbar = off;
   off += n4;
-  L.part = off;
-  off += align_up(3 * (size_t)kStatBlocks * 8);
-  L.res = off;
-  off += 256;
   L.total = off;
   return L;
 }
@@ -1473,8 +1469,6 @@ spg_status spg_vjp(spg_problem* P, void* d_vjp_ws, size_t bytes, const float* d_
   float* zbar = reinterpret_cast<float*>(ws + L.zbar);
   float* hz = reinterpret_cast<float*>(ws + L.hz);
   float* rbar = reinterpret_cast<float*>(ws + L.rbar);
-  double* part = reinterpret_cast<double*>(ws + L.part);
-  double* res = reinterpret_cast<double*>(ws + L.res);
   const float* u = P->unif_u ? nullptr : P->at<float>(P->lay.u);
   const float* v = P->unif_v ? nullptr : P->at<float>(P->lay.v);
   const double lr = P->lr;
@@ -1483,6 +1477,26 @@ spg_status spg_vjp(spg_problem* P, void* d_vjp_ws, size_t bytes, const float* d_
   SPG_CK(P, hipMemcpyAsync(abar(K), d_xbar, (size_t)d.nvox * 4, hipMemcpyDeviceToDevice, st));
   SPG_CK(P, launch_fill(abar(K - 1), d.nvox, 0.0f, st));
   double lamb = 0, mub = 0, lrb = 0;
+  // the steps' partial sums collect in the problem's partials and come to the host together,
+  // kStepsHeld steps at a time, so that the reverse walk does not wait for the GPU every step
+  constexpr int kStepStride = 3 * kStatBlocks, kStepsHeld = 80;
+  static_assert(kStepsHeld * (kStepStride + 3) <= kPartials, "partials of the held steps and their sums");
+  double* held = P->part();
+  double* sums = held + (size_t)kStepsHeld * kStepStride;
+  int nheld = 0, nt = 0;
+  auto settle = [&]() -> spg_status {
+    if (nheld == 0) return SPG_OK;
+    SPG_CK(P, launch_adj_sums(held, nheld, kStepStride, kStatBlocks, nt, sums, st));
+    double r[3 * kStepsHeld];
+    if (spg_status e = read_results_to(P, sums, r, 3 * nheld)) return e;
+    for (int i = 0; i < nheld; ++i) {
+      lamb += lr * r[3 * i];
+      lrb += P->prm.lambda * r[3 * i] - r[3 * i + 1] - P->prm.mu * r[3 * i + 2];
+      mub += -lr * r[3 * i + 2];
+    }
+    nheld = 0;
+    return SPG_OK;
+  };
   for (int sgm = L.nseg - 1; sgm >= 0; --sgm) {
     const int j0 = sgm * C;
     const int len = std::min(C, K - j0);
@@ -1499,20 +1513,16 @@ spg_status spg_vjp(spg_problem* P, void* d_vjp_ws, size_t bytes, const float* d_
     // reverse through the segment
     for (int i = len - 1; i >= 0; --i) {
       const int k = j0 + i;
+      double* part = held + (size_t)nheld * kStepStride;
       SPG_CK(P, launch_adj_prox(d, segx(i + 2), abar(k + 1), segg(i), u, (float)lr, zbar, rbar, part, kStatBlocks, st));
       if ((s = hessian_data(P, zbar, hz))) return s;
       SPG_CK(P, launch_adj_tv(d, segx(i + 1), segx(i), (float)P->vjp_m[k], zbar, hz, v, (float)lr,
                               (float)P->prm.mu, (float)P->prm.eps, abar(k), k >= 1 ? abar(k - 1) : nullptr,
-                              part + 2 * kStatBlocks, kStatBlocks, st));
-      const int ops[3] = {RED_OP_SUM, RED_OP_SUM, RED_OP_SUM};
-      SPG_CK(P, launch_reduce(part, kStatBlocks, 3, ops, res, st));
-      double r[3];
-      if ((s = read_results_to(P, res, r, 3))) return s;
-      lamb += lr * r[0];
-      lrb += P->prm.lambda * r[0] - r[1] - P->prm.mu * r[2];
-      mub += -lr * r[2];
+                              part + 2 * kStatBlocks, kStatBlocks, &nt, st));
+      if (++nheld == kStepsHeld && (s = settle())) return s;
     }
   }
+  if ((s = settle())) return s;
   // lr = 1/L(mu): d lr / d mu = -lr^2 max(v) ||D||^2 / eps
   mub += lrb * (-lr * lr * P->vmax * P->dn2 / P->prm.eps);
   // b-bar = w * A(rbar)

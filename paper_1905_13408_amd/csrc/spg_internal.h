@@ -33,8 +33,8 @@ constexpr int ST_PLAIN = 0, ST_COMP = 1, ST_BF16 = 2;
 
 // Arguments of the fused stencil / prox kernel.
 struct ProxArgs {
-  void* rbuf;                   // in: data gradient of y_k (real map); out: y_{k+1}
-                                // (fp32, bf16 in ST_BF16)
+  void* rbuf;                   // out: y_{k+1} (fp32, bf16 in ST_BF16)
+  const void* gsrc;             // data gradient of y_k (real map, as rbuf; may be rbuf)
   const float* gin;             // check mode: fp32 data gradient of x_k
   const float* xk_hi;           // x_k  (fp32 hi part)
   const uint16_t* xk_lo;        // x_k  (bf16 lo part; compensated mode only)
@@ -132,9 +132,12 @@ hipError_t launch_obj_finish(const double* pa, int na, const double* pc, int nc,
 hipError_t launch_reduce(const double* partials, int n, int nq, const int* ops, double* out, hipStream_t st);
 hipError_t launch_adj_prox(const Dims& d, const float* xn, const float* abar, const float* gdat, const float* u,
                            float lr, float* zbar, float* rbar, double* partials, int nblocks, hipStream_t st);
+// partials: one per block, at most max_blocks (>= 512)
 hipError_t launch_adj_tv(const Dims& d, const float* xk, const float* xkm, float m, const float* zbar, const float* hz,
                          const float* v, float lr, float mu, float eps, float* abar_k, float* abar_km,
-                         double* partials, int nblocks, hipStream_t st);
+                         double* partials, int max_blocks, int* nblocks_out, hipStream_t st);
+hipError_t launch_adj_sums(const double* partials, int steps, int stride, int nb, int nt, double* out,
+                           hipStream_t st);
 hipError_t launch_expand_bbar(const Dims& d, const float2* S, const float* w, float2* out, hipStream_t st);
 hipError_t launch_backproject(const Dims& d, int n_img, int m, const float2* images, const double* rots,
                               const float* ctf, const float* weights, double h, void* ws, size_t bytes, float* w,

@@ -1442,7 +1442,7 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
     for (int h = 0; h < NOWN; ++h) {
       const long long i = pz + own_off[h];
       if constexpr (CHECK) g[h] = vown[h] ? a.gin[i] : 0.f;
-      else g[h] = vown[h] ? ld_real<BF>(a.rbuf, i) : 0.f;
+      else g[h] = vown[h] ? ld_real<BF>(a.gsrc, i) : 0.f;
       uu[h] = (a.u && vown[h]) ? ld_real<BF>(a.u, i) : 1.0f;
       xp[h] = (a.xprev && vown[h]) ? a.xprev[i] : 0.f;
     }
@@ -2627,21 +2627,33 @@ __global__ void __launch_bounds__(256) k_fsc_final(const double* __restrict__ pa
 // y_k = x_k + m_k (x_k - x_{k-1}) (chain rule; a.e. derivatives at the kinks).
 
 // zbar = [x_{k+1} != 0] abar_{k+1};  rbar += lr zbar;  partials: sum tbar u with
-// tbar = -sign(x_{k+1}) zbar (threshold adjoint), and sum zbar g_data(y_k).
-__global__ void __launch_bounds__(256) k_adj_prox(long long n, const float* __restrict__ xn,
-                                                  const float* __restrict__ abar, const float* __restrict__ gdat,
-                                                  const float* __restrict__ u, float lr, float* __restrict__ zbar,
-                                                  float* __restrict__ rbar, double* __restrict__ partials) {
+// tbar = -sign(x_{k+1}) zbar (threshold adjoint), and sum zbar g_data(y_k).  n4 groups of four
+// voxels (every map starts on 256 bytes); bound by its seven passes over maps (16 bytes per
+// load: 10.1 us at 128^3, 15.3 with 4).
+__global__ void __launch_bounds__(256) k_adj_prox(long long n4, const float4* __restrict__ xn,
+                                                  const float4* __restrict__ abar, const float4* __restrict__ gdat,
+                                                  const float4* __restrict__ u, float lr, float4* __restrict__ zbar,
+                                                  float4* __restrict__ rbar, double* __restrict__ partials) {
   __shared__ double s_red[8];
   double s_t = 0.0, s_g = 0.0;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    const float x = xn[i];
-    const float zb = x != 0.f ? abar[i] : 0.f;
-    zbar[i] = zb;
-    rbar[i] += lr * zb;
-    const float uu = u ? u[i] : 1.0f;
-    s_t += -(double)copysignf(1.0f, x) * (x != 0.f ? (double)zb : 0.0) * uu;
-    s_g += (double)zb * gdat[i];
+  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n4; i += (long long)gridDim.x * blockDim.x) {
+    const float4 x4 = xn[i], a4 = abar[i], g4 = gdat[i];
+    float4 r4 = rbar[i];
+    const float4 u4 = u ? u[i] : make_float4(1.f, 1.f, 1.f, 1.f);
+    float4 z4;
+    auto one = [&](float x, float ab, float g, float uu, float& z, float& r) {
+      const float zb = x != 0.f ? ab : 0.f;
+      z = zb;
+      r += lr * zb;
+      s_t += -(double)copysignf(1.0f, x) * (x != 0.f ? (double)zb : 0.0) * uu;
+      s_g += (double)zb * g;
+    };
+    one(x4.x, a4.x, g4.x, u4.x, z4.x, r4.x);
+    one(x4.y, a4.y, g4.y, u4.y, z4.y, r4.y);
+    one(x4.z, a4.z, g4.z, u4.z, z4.z, r4.z);
+    one(x4.w, a4.w, g4.w, u4.w, z4.w, r4.w);
+    zbar[i] = z4;
+    rbar[i] = r4;
   }
   const int nb = gridDim.x;
   double r = block_reduce<RED_OP_SUM>(s_t, s_red);
@@ -2675,46 +2687,176 @@ __device__ __forceinline__ void adj_dual(const float d[3], const float e[3], flo
 
 // ybar = zbar - lr (hz + mu H_tv(y_k) zbar); abar_k += (1 + m) ybar; abar_{k-1} = -m ybar
 // (first contribution); partial: sum zbar g_tv(y_k).  y_k from the stored fp32 maps.
-// One thread per voxel, neighbours read through the cache (the reverse pass is not the
-// hot path).
+// Tiles of 64 x-columns by 8 y-rows marched along z over slabs of zc planes, as k_prox_tv:
+// an LDS ring of two planes of y and zbar with a halo, and one of two planes of the dual p and
+// its Hessian product q, so that a point's p and q are formed once instead of four times from
+// 48 reads through the cache (39.2 -> 25.8 us at 128^3).
 __global__ void __launch_bounds__(256) k_adj_tv(Dims dm, const float* __restrict__ xk, const float* __restrict__ xkm,
                                                 float m, const float* __restrict__ zbar, const float* __restrict__ hz,
                                                 const float* __restrict__ v, float lr, float mu, float eps,
                                                 float* __restrict__ abar_k, float* __restrict__ abar_km,
-                                                double* __restrict__ partials) {
+                                                double* __restrict__ partials, int ntx, int nty, int zc) {
+  constexpr int TX = PT_TX, TY = PT_TY;
+  constexpr int YW = TX + 2, YH = TY + 2;  // planes of y and zbar with halo
+  constexpr int PW = TX + 1, PH = TY + 1;  // planes of p and q with the +1 shell
+  constexpr int NPP = (PW * PH + 255) / 256;
+  constexpr int NHALO = 2 * YW + 2 * TY;
+  constexpr int NOWN = TY / 4;  // voxels per thread and plane: rows ty + 4 h
+  __shared__ float sY[2][YH][YW];
+  __shared__ float sZ[2][YH][YW];
+  __shared__ float sP[2][3][PH][PW];
+  __shared__ float sQ[2][3][PH][PW];
   __shared__ double s_red[8];
+  const int tid = threadIdx.x;
+  const int tx = tid & 63, ty = tid >> 6;
+  const int bx = blockIdx.x % ntx, by = (blockIdx.x / ntx) % nty, bz = blockIdx.x / (ntx * nty);
   const int nx = dm.nx, ny = dm.ny, nz = dm.nz;
+  const int x0 = bx * TX, y0 = by * TY;
+  const int z0 = bz * zc, z1 = min(z0 + zc, nz);
   const long long plane = (long long)nx * ny;
-  auto wr = [](int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); };
-  auto idx = [&](int z, int y, int x) { return (long long)wr(z, nz) * plane + (long long)wr(y, ny) * nx + wr(x, nx); };
-  auto Y = [&](long long i) { return xk[i] + m * (xk[i] - xkm[i]); };
-  auto point = [&](int z, int y, int x, float p[3], float q[3]) {
-    const long long i = idx(z, y, x);
-    const long long iz = idx(z - 1, y, x), iy = idx(z, y - 1, x), ix = idx(z, y, x - 1);
-    const float yc = Y(i), zc = zbar[i];
-    const float d[3] = {yc - Y(iz), yc - Y(iy), yc - Y(ix)};
-    const float e[3] = {zc - zbar[iz], zc - zbar[iy], zc - zbar[ix]};
-    adj_dual(d, e, v ? v[i] : 1.0f, eps, p, q);
-  };
-  double s_tv = 0.0;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < dm.nvox;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int x = (int)(i % nx), y = (int)((i / nx) % ny), z = (int)(i / plane);
-    float p0[3], q0[3], pz[3], qz[3], py[3], qy[3], px[3], qx[3];
-    point(z, y, x, p0, q0);
-    point(z + 1, y, x, pz, qz);
-    point(z, y + 1, x, py, qy);
-    point(z, y, x + 1, px, qx);
-    const float gtv = (p0[0] - pz[0]) + (p0[1] - py[1]) + (p0[2] - px[2]);
-    const float htv = (q0[0] - qz[0]) + (q0[1] - qy[1]) + (q0[2] - qx[2]);
-    const float zb = zbar[i];
-    s_tv += (double)zb * gtv;
-    const float yb = zb - lr * (hz[i] + mu * htv);
-    abar_k[i] += (1.0f + m) * yb;
-    if (abar_km) abar_km[i] = -m * yb;
+  auto wrapm = [](int c, int n) { return ((c % n) + n) % n; };
+  const int gx = wrapm(x0 + tx, nx);
+  int own_off[NOWN];
+  bool vown[NOWN];
+#pragma unroll
+  for (int h = 0; h < NOWN; ++h) {
+    own_off[h] = wrapm(y0 + ty + 4 * h, ny) * nx + gx;
+    vown[h] = (x0 + tx) < nx && (y0 + ty + 4 * h) < ny;
   }
-  double r = block_reduce<RED_OP_SUM>(s_tv, s_red);
+  const bool has_halo = tid < NHALO;
+  int hlx = 0, hly = 0;
+  if (tid < YW) { hly = -1; hlx = tid - 1; }
+  else if (tid < 2 * YW) { hly = TY; hlx = tid - YW - 1; }
+  else if (tid < 2 * YW + TY) { hlx = -1; hly = tid - 2 * YW; }
+  else { hlx = TX; hly = tid - 2 * YW - TY; }
+  const int halo_off = wrapm(y0 + hly, ny) * nx + wrapm(x0 + hlx, nx);
+  int p_off[NPP];
+  bool p_ok[NPP];
+#pragma unroll
+  for (int t = 0; t < NPP; ++t) {
+    const int idx = tid + 256 * t;
+    p_ok[t] = idx < PW * PH;
+    const int ly = idx / PW, lx = idx - ly * PW;
+    p_off[t] = wrapm(y0 + ly, ny) * nx + wrapm(x0 + lx, nx);
+  }
+  struct Raw {
+    float xk[NOWN + 1], xm[NOWN + 1], zb[NOWN + 1], v[NPP];  // own voxels, then the halo point
+  };
+  auto fetch = [&](int zz, Raw& r) {
+    const long long pz = (long long)wrapm(zz, nz) * plane;
+#pragma unroll
+    for (int h = 0; h <= NOWN; ++h) {
+      if (h == NOWN && !has_halo) continue;
+      const long long i = pz + (h < NOWN ? own_off[h < NOWN ? h : 0] : halo_off);
+      r.xk[h] = xk[i];
+      r.xm[h] = xkm[i];
+      r.zb[h] = zbar[i];
+    }
+#pragma unroll
+    for (int t = 0; t < NPP; ++t) r.v[t] = v && p_ok[t] ? v[pz + p_off[t]] : 1.0f;
+  };
+  auto store = [&](int buf, const Raw& r) {
+#pragma unroll
+    for (int h = 0; h < NOWN; ++h) {
+      sY[buf][ty + 4 * h + 1][tx + 1] = r.xk[h] + m * (r.xk[h] - r.xm[h]);
+      sZ[buf][ty + 4 * h + 1][tx + 1] = r.zb[h];
+    }
+    if (has_halo) {
+      sY[buf][hly + 1][hlx + 1] = r.xk[NOWN] + m * (r.xk[NOWN] - r.xm[NOWN]);
+      sZ[buf][hly + 1][hlx + 1] = r.zb[NOWN];
+    }
+  };
+  // p and q of a plane from planes c (this one) and b (below) into slot dst
+  auto duals = [&](int c, int b, int dst, const float* vv) {
+#pragma unroll
+    for (int t = 0; t < NPP; ++t) {
+      if (!p_ok[t]) continue;
+      const int idx = tid + 256 * t;
+      const int ly = idx / PW, lx = idx - ly * PW;
+      const float yc = sY[c][ly + 1][lx + 1], zc_ = sZ[c][ly + 1][lx + 1];
+      const float d[3] = {yc - sY[b][ly + 1][lx + 1], yc - sY[c][ly][lx + 1], yc - sY[c][ly + 1][lx]};
+      const float e[3] = {zc_ - sZ[b][ly + 1][lx + 1], zc_ - sZ[c][ly][lx + 1], zc_ - sZ[c][ly + 1][lx]};
+      float p[3], q[3];
+      adj_dual(d, e, vv[t], eps, p, q);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        sP[dst][a][ly][lx] = p[a];
+        sQ[dst][a][ly][lx] = q[a];
+      }
+    }
+  };
+  Raw r0, r1;
+  fetch(z0 - 1, r0);
+  fetch(z0, r1);
+  store(0, r0);
+  store(1, r1);
+  float zb_own[NOWN], vv[NPP];
+#pragma unroll
+  for (int h = 0; h < NOWN; ++h) zb_own[h] = r1.zb[h];
+  __syncthreads();
+  duals(1, 0, 0, r1.v);
+  fetch(z0 + 1, r0);
+  __syncthreads();  // the first step rewrites the plane z0 - 1
+  double s_tv = 0.0;
+  int cur = 0, yc = 1;
+  for (int z = z0; z < z1; ++z) {
+    store(yc ^ 1, r0);
+    float zb_nxt[NOWN], hzv[NOWN], ab[NOWN];
+#pragma unroll
+    for (int h = 0; h < NOWN; ++h) zb_nxt[h] = r0.zb[h];
+#pragma unroll
+    for (int t = 0; t < NPP; ++t) vv[t] = r0.v[t];
+    const long long pz = (long long)z * plane;
+#pragma unroll
+    for (int h = 0; h < NOWN; ++h) {
+      hzv[h] = vown[h] ? hz[pz + own_off[h]] : 0.f;
+      ab[h] = vown[h] ? abar_k[pz + own_off[h]] : 0.f;
+    }
+    if (z + 1 < z1) fetch(z + 2, r0);
+    __syncthreads();
+    duals(yc ^ 1, yc, cur ^ 1, vv);
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < NOWN; ++h) {
+      const int ly = ty + 4 * h, lx = tx;
+      if (vown[h]) {
+        const float gtv = (sP[cur][0][ly][lx] - sP[cur ^ 1][0][ly][lx]) +
+                          (sP[cur][1][ly][lx] - sP[cur][1][ly + 1][lx]) +
+                          (sP[cur][2][ly][lx] - sP[cur][2][ly][lx + 1]);
+        const float htv = (sQ[cur][0][ly][lx] - sQ[cur ^ 1][0][ly][lx]) +
+                          (sQ[cur][1][ly][lx] - sQ[cur][1][ly + 1][lx]) +
+                          (sQ[cur][2][ly][lx] - sQ[cur][2][ly][lx + 1]);
+        const long long i = pz + own_off[h];
+        const float zb = zb_own[h];
+        s_tv += (double)zb * gtv;
+        const float yb = zb - lr * (hzv[h] + mu * htv);
+        abar_k[i] = ab[h] + (1.0f + m) * yb;
+        if (abar_km) abar_km[i] = -m * yb;
+      }
+    }
+    cur ^= 1;
+    yc ^= 1;
+#pragma unroll
+    for (int h = 0; h < NOWN; ++h) zb_own[h] = zb_nxt[h];
+  }
+  const double r = block_reduce<RED_OP_SUM>(s_tv, s_red);
   if (threadIdx.x == 0) partials[blockIdx.x] = r;
+}
+
+// Sums of the three partial groups of each reverse step (steps of `stride` words: 2 nb words
+// of k_adj_prox, then nt of k_adj_tv), one block per step, in a fixed order: out[3 step + q].
+__global__ void __launch_bounds__(256) k_adj_sums(const double* __restrict__ partials, int stride, int nb, int nt,
+                                                  double* __restrict__ out) {
+  __shared__ double s_red[8];
+  const double* __restrict__ p = partials + (long long)blockIdx.x * stride;
+  for (int g = 0; g < 3; ++g) {
+    const double* __restrict__ q = p + (g < 2 ? g * nb : 2 * nb);
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < (g < 2 ? nb : nt); i += 256) acc += q[i];
+    const double r = block_reduce<RED_OP_SUM>(acc, s_red);
+    if (threadIdx.x == 0) out[3 * blockIdx.x + g] = r;
+    __syncthreads();
+  }
 }
 
 // Full complex b-bar = w * A(rbar) / (unitary A) from the packed half spectrum of rbar
@@ -3626,14 +3768,27 @@ hipError_t launch_fsc_shells(const Dims& d, const float2* S1, const float2* S2, 
 
 hipError_t launch_adj_prox(const Dims& d, const float* xn, const float* abar, const float* gdat, const float* u,
                            float lr, float* zbar, float* rbar, double* partials, int nblocks, hipStream_t st) {
-  k_adj_prox<<<nblocks, 256, 0, st>>>(d.nvox, xn, abar, gdat, u, lr, zbar, rbar, partials);
+  auto q = [](const float* p) { return reinterpret_cast<const float4*>(p); };
+  k_adj_prox<<<nblocks, 256, 0, st>>>(d.nvox / 4, q(xn), q(abar), q(gdat), q(u), lr, reinterpret_cast<float4*>(zbar),
+                                      reinterpret_cast<float4*>(rbar), partials);
   return hipGetLastError();
 }
 
 hipError_t launch_adj_tv(const Dims& d, const float* xk, const float* xkm, float m, const float* zbar, const float* hz,
                          const float* v, float lr, float mu, float eps, float* abar_k, float* abar_km,
-                         double* partials, int nblocks, hipStream_t st) {
-  k_adj_tv<<<nblocks, 256, 0, st>>>(d, xk, xkm, m, zbar, hz, v, lr, mu, eps, abar_k, abar_km, partials);
+                         double* partials, int max_blocks, int* nblocks_out, hipStream_t st) {
+  const int ntx = (d.nx + PT_TX - 1) / PT_TX, nty = (d.ny + PT_TY - 1) / PT_TY;
+  int zc = 4;  // the shallowest slabs that keep within the partials
+  while ((long long)ntx * nty * ((d.nz + zc - 1) / zc) > max_blocks) zc *= 2;
+  *nblocks_out = ntx * nty * ((d.nz + zc - 1) / zc);
+  k_adj_tv<<<*nblocks_out, 256, 0, st>>>(d, xk, xkm, m, zbar, hz, v, lr, mu, eps, abar_k, abar_km, partials, ntx, nty,
+                                         zc);
+  return hipGetLastError();
+}
+
+hipError_t launch_adj_sums(const double* partials, int steps, int stride, int nb, int nt, double* out,
+                           hipStream_t st) {
+  k_adj_sums<<<steps, 256, 0, st>>>(partials, stride, nb, nt, out);
   return hipGetLastError();
 }
 
