@@ -45,14 +45,22 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 
 // Element i of a real array stored as fp32 or (BF) bf16.
 template <bool BF>
-__device__ __forceinline__ float ld_real(const void* p, long long i) {
-  if constexpr (BF) return bf16_to_f32(reinterpret_cast<const uint16_t*>(p)[i]);
-  else return reinterpret_cast<const float*>(p)[i];
-}
-template <bool BF>
 __device__ __forceinline__ void st_real(void* p, long long i, float v) {
   if constexpr (BF) reinterpret_cast<uint16_t*>(p)[i] = f32_to_bf16(v);
   else reinterpret_cast<float*>(p)[i] = v;
+}
+
+// The stored word of a real array, for loads requested ahead of their use: a bf16 word
+// widened at once would make the wave wait for the load where it is issued.
+template <bool BF>
+using RealWord = typename std::conditional<BF, uint16_t, float>::type;
+__device__ __forceinline__ float widen(float v) { return v; }
+__device__ __forceinline__ float widen(uint16_t v) { return bf16_to_f32(v); }
+constexpr uint16_t kBf16One = 0x3F80;
+template <bool BF>
+__device__ __forceinline__ RealWord<BF> word_one() {
+  if constexpr (BF) return kBf16One;
+  else return 1.0f;
 }
 
 // ---------------------------------------------------------------- radix butterflies
@@ -1375,6 +1383,8 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
   constexpr int NHALO = 2 * YW + 2 * TY;
   constexpr int NOWN = TY / 4;  // voxels per thread and plane: rows ty + 4 h
   static_assert(TY % 4 == 0 && NHALO <= 256, "tile shape");
+  using W = RealWord<BF>;                                                     // u and v
+  using WG = typename std::conditional<CHECK, float, RealWord<BF>>::type;     // the gradient
   __shared__ float sY[2][YH][YW];
   __shared__ float sP[2][3][PH][PW];
   __shared__ double s_red[8];
@@ -1427,23 +1437,23 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
   }
 
   auto pz_of = [&](int zz) { return (long long)(zz < 0 ? zz + nz : (zz >= nz ? zz - nz : zz)) * plane; };
-  auto fetch_plane = [&](int zz, RawX* own, RawX& halo, float* vv) {
+  auto fetch_plane = [&](int zz, RawX* own, RawX& halo, W* vv) {
     const long long pz = pz_of(zz);
 #pragma unroll
     for (int h = 0; h < NOWN; ++h) fetch_raw<COMP>(a, pz + own_off[h], own[h]);
     if (has_halo) fetch_raw<COMP>(a, pz + halo_off, halo);
 #pragma unroll
-    for (int t = 0; t < NPP; ++t) vv[t] = (a.v && p_ok[t]) ? ld_real<BF>(a.v, pz + p_off[t]) : 1.0f;
+    for (int t = 0; t < NPP; ++t) vv[t] = (a.v && p_ok[t]) ? reinterpret_cast<const W*>(a.v)[pz + p_off[t]] : word_one<BF>();
   };
   // inputs of the outputs of plane zz: data gradient, l1 weight and (gamma term) prior map
-  auto fetch_out = [&](int zz, float* g, float* uu, float* xp) {
+  auto fetch_out = [&](int zz, WG* g, W* uu, float* xp) {
     const long long pz = (long long)zz * plane;
 #pragma unroll
     for (int h = 0; h < NOWN; ++h) {
       const long long i = pz + own_off[h];
       if constexpr (CHECK) g[h] = vown[h] ? a.gin[i] : 0.f;
-      else g[h] = vown[h] ? ld_real<BF>(a.gsrc, i) : 0.f;
-      uu[h] = (a.u && vown[h]) ? ld_real<BF>(a.u, i) : 1.0f;
+      else g[h] = vown[h] ? reinterpret_cast<const W*>(a.gsrc)[i] : W(0);
+      uu[h] = (a.u && vown[h]) ? reinterpret_cast<const W*>(a.u)[i] : word_one<BF>();
       xp[h] = (a.xprev && vown[h]) ? a.xprev[i] : 0.f;
     }
   };
@@ -1465,7 +1475,7 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
 
   double acc_l1 = 0.0, acc_hub = 0.0, acc_tv0 = 0.0, acc_kkt = 0.0, acc_x2 = 0.0, acc_gam = 0.0;
   // p on the (TX+1) x (TY+1) points of a plane from y planes yn (this plane) and yp (below).
-  auto compute_p = [&](int yn, int yp, int dst, const float* vv, bool count) {
+  auto compute_p = [&](int yn, int yp, int dst, const W* vv, bool count) {
 #pragma unroll
     for (int t = 0; t < NPP; ++t) {
       if (!p_ok[t]) continue;
@@ -1478,7 +1488,8 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
       // v / max(eps, |Dy|) with one reciprocal square root
       const float n2 = dxv * dxv + dyv * dyv + dzv * dzv;
       const float inv = inv_norm(a, n2);
-      const float sc = vv[t] * inv;
+      const float vt = widen(vv[t]);
+      const float sc = vt * inv;
       sP[dst][0][ly][lx] = sc * dzv;
       sP[dst][1][ly][lx] = sc * dyv;
       sP[dst][2][ly][lx] = sc * dxv;
@@ -1487,21 +1498,23 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
           const double nd = sqrt((double)n2);
           const double e = a.eps;
           const double hub = nd < e ? nd * nd / (2.0 * e) : nd - 0.5 * e;
-          acc_hub += (double)vv[t] * hub;
-          acc_tv0 += (double)vv[t] * nd;
+          acc_hub += (double)vt * hub;
+          acc_tv0 += (double)vt * nd;
         }
       } else if constexpr (MON) {
         if (count && lx < TX && ly < TY && (x0 + lx) < nx && (y0 + ly) < ny)
-          acc_hub += (double)vv[t] * huber64(n2, a.eps);
+          acc_hub += (double)vt * huber64(n2, a.eps);
       }
     }
   };
 
   // ---- prologue: planes z0-1 and z0 into LDS, p(z0), and the first prefetches
   RawX rown[NOWN], rhalo;
-  float rv[NPP];
+  W rv[NPP];
   double own_y[NOWN], own_xk[NOWN], nxt_y[NOWN], nxt_xk[NOWN];
-  float g_cur[NOWN], u_cur[NOWN], xp_cur[NOWN];
+  WG g_cur[NOWN];
+  W u_cur[NOWN];
+  float xp_cur[NOWN];
   {
     double dy_[NOWN], dx_[NOWN];
     fetch_plane(z0 - 1, rown, rhalo, rv);
@@ -1519,10 +1532,12 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
   for (int z = z0; z < z1; ++z) {
     // y of plane z+1 from the words fetched during the previous step
     store_plane(ycur ^ 1, rown, rhalo, nxt_y, nxt_xk);
-    float vv_use[NPP];
+    W vv_use[NPP];
 #pragma unroll
     for (int t = 0; t < NPP; ++t) vv_use[t] = rv[t];
-    float g_use[NOWN], u_use[NOWN], xp_use[NOWN];
+    WG g_use[NOWN];
+    W u_use[NOWN];
+    float xp_use[NOWN];
 #pragma unroll
     for (int h = 0; h < NOWN; ++h) {
       g_use[h] = g_cur[h];
@@ -1545,8 +1560,8 @@ __global__ void __launch_bounds__(256) k_prox_tv(ProxArgs a, int ntx, int nty) {
                         sP[cur][1][ly + 1][lx] - sP[cur ^ 1][0][ly][lx];
       if (vown[h]) {
         const long long i = pz + own_off[h];
-        const float gd = g_use[h];
-        const float uu = u_use[h];
+        const float gd = widen(g_use[h]);
+        const float uu = widen(u_use[h]);
         const float xp = xp_use[h];
         if constexpr (COMP) {
           const double y = own_y[h];
@@ -1685,7 +1700,7 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
   constexpr int FT = PfT<M>::T, FE = PfT<M>::E;
   constexpr int NR = KB * TY;  // rows of one batch
   constexpr int NG = PIPE ? 3 : 1;  // batches of rows in LDS
-  using VT = typename std::conditional<BF, uint16_t, float>::type;  // penalty-weight word
+  using VT = RealWord<BF>;  // penalty-weight word
   constexpr int NO = TY / 2;  // own rows per thread
   static_assert(TY % 2 == 0 && 2 * NR * FT == (PIPE ? NX : 2 * NX), "one transform row share per thread");
   static_assert(!PIPE || (FE == 8 && 64 % FT == 0 && RegPlan<M, FT>::ns == 3),
@@ -1740,10 +1755,8 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
     w.oh = ld_at(xo_hi + pz, o * 4u);
     if constexpr (COMP) w.ol = ld_at(xo_lo + pz, o * 2u);
   };
-  auto ld_w = [&](const void* base, long long pz, unsigned o) -> float {
-    const VT* b = reinterpret_cast<const VT*>(base) + pz;
-    if constexpr (BF) return bf16_to_f32(ld_at(b, o * 2u));
-    else return ld_at(b, o * 4u);
+  auto ld_w = [&](const void* base, long long pz, unsigned o) -> VT {
+    return ld_at(reinterpret_cast<const VT*>(base) + pz, o * (unsigned)sizeof(VT));
   };
   auto fetch_x = [&](int zz, RawX* own, RawX& halo) {
     const long long pz = pz_of(zz);
@@ -1751,23 +1764,23 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
     for (int h = 0; h < NO; ++h) fetch_one(pz, own_off[h], own[h]);
     fetch_one(pz, halo_off, halo);
   };
-  auto fetch_v = [&](int zz, float* vv) {
+  auto fetch_v = [&](int zz, VT* vv) {
     const long long pz = pz_of(zz);
     if (a.v) {
 #pragma unroll
       for (int h = 0; h < NO; ++h) vv[h] = ld_w(a.v, pz, own_off[h]);
-      vv[NO] = r == 1 ? ld_w(a.v, pz, halo_off) : 1.0f;
+      vv[NO] = r == 1 ? ld_w(a.v, pz, halo_off) : word_one<BF>();
     } else {
 #pragma unroll
-      for (int h = 0; h <= NO; ++h) vv[h] = 1.0f;
+      for (int h = 0; h <= NO; ++h) vv[h] = word_one<BF>();
     }
   };
-  auto fetch_out = [&](int zz, float* uu, float* xq) {
+  auto fetch_out = [&](int zz, VT* uu, float* xq) {
     long long pz = (long long)zz * plane;
     asm volatile("" : "+s"(pz));
 #pragma unroll
     for (int h = 0; h < NO; ++h) {
-      uu[h] = a.u ? ld_w(a.u, pz, own_off[h]) : 1.0f;
+      uu[h] = a.u ? ld_w(a.u, pz, own_off[h]) : word_one<BF>();
       if constexpr (PRIOR) xq[h] = ld_at(a.xprev + pz, own_off[h] * 4u);
       else xq[h] = 0.f;
     }
@@ -1826,18 +1839,18 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
   double acc_l1 = 0.0, acc_hub = 0.0, acc_gam = 0.0;
   // sc = v / max(eps, |Dy|): writes the ring slot of plane zz and returns the thread's own
   // values in sco
-  auto compute_sc = [&](int zz, const float* vv, float* sco) {
+  auto compute_sc = [&](int zz, const VT* vv, float* sco) {
     float(*SC)[NX] = sSC[zz & 1];
 #pragma unroll
     for (int h = 0; h < NO; ++h) {
       const float n2 = n2_at(zz, r + 2 * h);
-      sco[h] = vv[h] * inv_norm(a, n2);
+      sco[h] = widen(vv[h]) * inv_norm(a, n2);
       SC[r + 2 * h][x] = sco[h];
       if constexpr (MON) {
-        if (zz < z1) acc_hub += (double)vv[h] * huber64(n2, a.eps);
+        if (zz < z1) acc_hub += (double)widen(vv[h]) * huber64(n2, a.eps);
       }
     }
-    if (r == 1) SC[TY][x] = vv[NO] * inv_norm(a, n2_at(zz, TY));
+    if (r == 1) SC[TY][x] = widen(vv[NO]) * inv_norm(a, n2_at(zz, TY));
   };
   // One transform phase.  Forward half (fr < NR): the y_{k+1} rows of the batch at plane
   // zf (planes < zf_end) from sG into S.  Inverse half: the spectrum rows in `sa` of the
@@ -1918,9 +1931,10 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
   // ---- one plane step, first half: y of plane z+1 from the words fetched during the
   // previous step into the ring; the words of plane z+2 are requested at once
   RawX rown[NO], rhalo;
-  float rv[NO + 1];
+  VT rv[NO + 1];
   double own_y[NO], own_xk[NO], nxt_y[NO], nxt_xk[NO];
-  float u_cur[NO], xq_cur[NO], u_nxt[NO], xq_nxt[NO];
+  VT u_cur[NO], u_nxt[NO];
+  float xq_cur[NO], xq_nxt[NO];
   auto step_a = [&](int z) {
     // The lane indices pass through empty asm statements so that the LDS and global
     // addresses derived from them are formed inside the loop where they are used, not
@@ -1965,7 +1979,7 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
         const float pzn = __fmul_rn(sc1[h], Y1[ly + 1][x] - yc);
         const float gtv = pzc + pyc + pxc - pxn - pyn - pzn;
         const float gd = G[ly][x];
-        const float uu = u_cur[h];
+        const float uu = widen(u_cur[h]);
         const float xq = xq_cur[h];
         float ynext;
         if constexpr (COMP) {
