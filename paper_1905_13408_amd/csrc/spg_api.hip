@@ -563,9 +563,11 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
   const Dims& d = P->d;
   {
     if (!P->primed) {
-      SPG_CK(P, launch_prime(d, P->rbuf(), P->xhi(P->cur), P->xlo(P->cur), P->xhi(P->old), P->xlo(P->old),
-                             P->m_cur, P->m_cur != 0.0, P->store, P->stream));
-      if ((s = r2c(P, P->rbuf(), P->bf()))) return s;
+      prof_begin(P, SPG_KERNEL_R2C_X);
+      SPG_CK(P, launch_prime(d, P->xhi(P->cur), P->xlo(P->cur), P->xhi(P->old), P->xlo(P->old), P->m_cur,
+                             P->m_cur != 0.0, P->store, P->S(), P->at<float2>(P->lay.tw_m),
+                             P->at<float2>(P->lay.tw_n), P->stream));
+      prof_end(P, SPG_KERNEL_R2C_X);
       P->primed = true;
     }
     const bool fuse = P->fused && !capture_g;

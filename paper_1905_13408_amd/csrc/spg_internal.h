@@ -104,9 +104,11 @@ hipError_t launch_c2r_x(const Dims& d, const float2* S, void* rout, bool rout_bf
 hipError_t launch_prox_tv(const Dims& d, const ProxArgs& a, int store, bool check, hipStream_t st,
                           bool mon = false);
 
-hipError_t launch_prime(const Dims& d, void* rbuf, const float* xk_hi, const uint16_t* xk_lo,
-                        const float* xo_hi, const uint16_t* xo_lo, double m, int read_old,
-                        int store, hipStream_t st);
+// x-axis forward transforms of y = x_k + m (x_k - x_{k-1}) from the iterate words (the first
+// of a round)
+hipError_t launch_prime(const Dims& d, const float* xk_hi, const uint16_t* xk_lo, const float* xo_hi,
+                        const uint16_t* xo_lo, double m, int read_old, int store, float2* S, const float2* tw_m,
+                        const float2* tw_n, hipStream_t st);
 hipError_t launch_set_map(const Dims& d, const float* x0, float* hi, uint16_t* lo, hipStream_t st);
 hipError_t launch_get_map(const Dims& d, const float* hi, const uint16_t* lo, float* out, bool compensated,
                           hipStream_t st);
