@@ -38,7 +38,7 @@ bool pow2_in(int n, int lo, int hi) { return n >= lo && n <= hi && (n & (n - 1))
 bool axis_ok(int n) { return pow2_in(n, 4, 512) || n == 160 || n == 192; }
 
 struct Layout {
-  size_t xhi[3], xlo[3], u, v, S, rbuf, xprev, ws, wnyq, cs, cnyq, tw_m, tw_n, tw_y, tw_z, part, res, hist,
+  size_t xhi[3], xlo[3], u, v, S, rbuf, xprev, ws, wnyq, cs, cnyq, w0p, c0p, tw_m, tw_n, tw_y, tw_z, part, res, hist,
       total;
 };
 
@@ -65,6 +65,8 @@ Layout make_layout(const spg_params& p) {
   L.wnyq = take((size_t)p.nz * p.ny * 4);
   L.cs = take((size_t)p.nz * p.ny * P * 8);
   L.cnyq = take((size_t)p.nz * p.ny * 8);
+  L.w0p = p.nz == 512 ? take((size_t)p.nz * p.ny * 4) : 0;  // see dc_plane_apart
+  L.c0p = p.nz == 512 ? take((size_t)p.nz * p.ny * 8) : 0;
   L.tw_m = take(P * 8);
   L.tw_n = take((size_t)p.nx * 8);
   L.tw_y = take((size_t)p.ny * 8);
@@ -283,7 +285,9 @@ spg_status read_results(spg_problem* P, double* host, int n) {
 }
 
 FoldedData folded(spg_problem* P) {
-  return {P->at<float>(P->lay.ws), P->at<float2>(P->lay.cs), P->at<float>(P->lay.wnyq), P->at<float2>(P->lay.cnyq)};
+  const bool apart = dc_plane_apart(P->d);
+  return {P->at<float>(P->lay.ws), P->at<float2>(P->lay.cs), P->at<float>(P->lay.wnyq), P->at<float2>(P->lay.cnyq),
+          apart ? P->at<float>(P->lay.w0p) : nullptr, apart ? P->at<float2>(P->lay.c0p) : nullptr};
 }
 
 // The y, z passes with the weight step on the x-spectrum rows in S (the forward x
@@ -470,8 +474,10 @@ spg_status spg_set_data(spg_problem* P, const float* d_w, const float* d_b) {
   if (r[0] > 0) return set_err(P, SPG_E_NONFINITE, "w or b holds NaN/Inf values");
   if (r[1] < 0) return set_err(P, SPG_E_INVAL, "negative Fourier weight");
   // 2. fold onto the packed half spectrum
+  const bool apart = dc_plane_apart(d);
   SPG_CK(P, launch_fold(d, d_w, b, P->at<float>(P->lay.ws), P->at<float>(P->lay.wnyq), P->at<float2>(P->lay.cs),
-                        P->at<float2>(P->lay.cnyq), part, kStatBlocks, P->stream));
+                        P->at<float2>(P->lay.cnyq), apart ? P->at<float>(P->lay.w0p) : nullptr,
+                        apart ? P->at<float2>(P->lay.c0p) : nullptr, part, kStatBlocks, P->stream));
   const int ops1[1] = {RED_OP_MAX};
   SPG_CK(P, launch_reduce(part, kStatBlocks, 1, ops1, P->res(), P->stream));
   double mx;
@@ -1395,7 +1401,7 @@ spg_status hessian_data(spg_problem* P, const float* in, float* out) {
   SPG_CK(P, launch_r2c_x(d, in, false, P->S(), P->at<float2>(P->lay.tw_m), P->at<float2>(P->lay.tw_n), st));
   SPG_CK(P, launch_fft_cols(d, P->S(), 1, 0, P->at<float2>(P->lay.tw_y), nullptr, nullptr, st, nullptr));
   FoldedData fd = folded(P);
-  fd.cs = fd.cnyq = nullptr;
+  fd.cs = fd.cnyq = fd.c0p = nullptr;
   SPG_CK(P, launch_fft_cols(d, P->S(), 2, 4, P->at<float2>(P->lay.tw_z), &fd, nullptr, st, nullptr));
   if (dc_plane_apart(d))
     SPG_CK(P, launch_dc_nyquist(d, P->S(), P->at<float2>(P->lay.tw_z), fd, nullptr, st, nullptr));

@@ -71,13 +71,15 @@ int prox_fft_num_blocks(const Dims& d, int zc);
 hipError_t launch_prox_fft(const Dims& d, const ProxArgs& a, float2* S, const float2* tw_m, const float2* tw_n,
                            int store, hipStream_t st, bool mon = false);
 
-// Folded weights and data terms of the z pass (cs and cnyq null for mode 4): the packed half
+// Folded weights and data terms of the z pass (cs, cnyq and c0p null for mode 4): the packed half
 // spectrum's, and those of the plane kx = nx/2 that shares its slot 0 with kx = 0.
 struct FoldedData {
   const float* ws;
   const float2* cs;
   const float* wnyq;
   const float2* cnyq;
+  const float* w0p;  // those of kx = 0 again, for the plane's own launch (null elsewhere)
+  const float2* c0p;
 };
 
 // persist: the fused z modes run persistent blocks (false: one block per tile, for
@@ -113,7 +115,7 @@ hipError_t launch_set_map(const Dims& d, const float* x0, float* hi, uint16_t* l
 hipError_t launch_get_map(const Dims& d, const float* hi, const uint16_t* lo, float* out, bool compensated,
                           hipStream_t st);
 hipError_t launch_fold(const Dims& d, const float* w, const float2* b, float* ws, float* wnyq, float2* cs,
-                       float2* cnyq, double* partials, int nblocks, hipStream_t st);
+                       float2* cnyq, float* w0p, float2* c0p, double* partials, int nblocks, hipStream_t st);
 // partials: 5 x nblocks (non-finite count, min w, 1/2 sum w|b|^2, sum w, energy of the
 // real part of the unregularised solution)
 hipError_t launch_data_stats(const Dims& d, const float* w, const float2* b, double* partials, int nblocks,
