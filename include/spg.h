@@ -219,7 +219,9 @@ spg_status spg_set_state(spg_problem* P, const void* d_buf, size_t bytes);
  * weights as set, with HIP events, each candidate twice (two sweeps, the faster time
  * counts), and keeps the fastest; it leaves the map at 0 with the momentum restarted.
  * Defaults: 16, 16 and a slab depth of 32 planes, halved (down to 4) while the stencil
- * kernel would run fewer than 512 blocks (small maps).  Results are bitwise independent of
+ * kernel would run fewer than 512 blocks (small maps); the fused path (see spg_set_fusion)
+ * picks a slab depth of its own, not reported here, until spg_set_launch_shape is called, and
+ * the autotuner keeps that one where it measures fastest.  Results are bitwise independent of
  * the launch shape. */
 spg_status spg_set_launch_shape(spg_problem* P, int32_t nt_y, int32_t nt_z, int32_t zc);
 spg_status spg_get_launch_shape(const spg_problem* P, int32_t* nt_y, int32_t* nt_z, int32_t* zc);
@@ -235,10 +237,9 @@ spg_status spg_autotune(spg_problem* P, int32_t iters);
  * SPG_FLAG_BF16_STORAGE the fused path keeps the gradient and extrapolated rows in fp32.
  * spg_set_fusion(P, 1) on a grid without support returns SPG_E_UNSUPPORTED; 0 selects
  * the separate sweeps, which spg_autotune then keeps (it may turn the fused path off where
- * the separate sweeps measure faster, never on).  On nx = 160 the library picks the path and,
- * until a launch shape is set or tuned, the slab depth itself (fused but with
- * SPG_FLAG_BF16_STORAGE): spg_get_fusion reports 0 there and spg_set_fusion(P, 0) changes
- * nothing.  Iterations of spg_run_checkpointed and the
+ * the separate sweeps measure faster, never on).  On nx = 160 the library picks the path
+ * itself (fused but with SPG_FLAG_BF16_STORAGE): spg_get_fusion reports 0 there and
+ * spg_set_fusion(P, 0) changes nothing.  Iterations of spg_run_checkpointed and the
  * replays of spg_vjp always use the separate sweeps (the replays keep the data gradient of
  * every iteration), so that the recorded and replayed trajectories agree bitwise; the
  * setting is restored afterwards. */

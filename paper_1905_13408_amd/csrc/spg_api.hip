@@ -158,7 +158,7 @@ struct spg_problem {
   // launch shapes (chosen by spg_autotune): columns per tile of the y and z passes, z-slab
   // depth of the stencil kernel
   int nt_y = 16, nt_z = 16, zc = PT_ZC;
-  int zc_own = 0;  // slab depth of a path that picks its own while no launch shape has been set (0: zc)
+  int zc_own = 0;  // the fused path's own slab depth while no launch shape has been set (0: zc)
   bool fused = false;  // fused x-axis transforms in the stencil/prox kernel
   bool shared_gpu = false;  // being captured into a batch graph with other problems
   // unrolled solve recorded by spg_run_checkpointed for spg_vjp
@@ -433,10 +433,10 @@ spg_status spg_create(const spg_params* p, void* d_workspace, size_t bytes, void
   P->store = P->comp ? ST_COMP : ((p->flags & SPG_FLAG_BF16_STORAGE) ? ST_BF16 : ST_PLAIN);
   P->dn2 = dnorm2_of(p->nx, p->ny, p->nz);
   P->fused = prox_fft_runs(P->d, P->store);
-  if (P->fused && !prox_fft_supported(P->d)) P->zc_own = prox_fft_slab(P->d);
-  // z-slab depth of the stencil kernel: 32 planes, or fewer on small maps, whose blocks
-  // (ny / 4 tiles per slab) would otherwise be too few to keep more than a few CUs busy and
-  // each march through many planes in turn
+  if (P->fused) P->zc_own = prox_fft_slab(P->d);
+  // nominal z-slab depth of the stencil kernel, and the separate path's: 32 planes, or fewer on
+  // small maps, whose blocks (ny / 4 tiles per slab) would otherwise be too few to keep more
+  // than a few CUs busy and each march through many planes in turn
   while (P->zc > 4 && (long long)(p->ny / 4) * ((p->nz + P->zc - 1) / P->zc) < 512) P->zc /= 2;
   P->mon_every = (p->flags & SPG_FLAG_MONITOR) ? p->obj_every : 0;
   P->hist_iter.assign(kHistCap, 0);
@@ -1050,22 +1050,33 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
     std::vector<int> cand;
   };
   int fused = P->fused ? 1 : 0;
-  P->zc_own = 0;
+  // the slab depth of the fused path may also stay the one it picks itself (candidate 0): then
+  // the depth that is reported is the best of the others
+  const int own = P->fused ? prox_fft_slab(P->d) : 0;
+  int zsel = own ? 0 : P->zc;
+  auto set_depth = [&]() {
+    P->zc_own = zsel == 0 ? own : 0;
+    if (zsel) P->zc = zsel;
+  };
+  set_depth();
   std::vector<Knob> knobs = {{&P->nt_y, {SPG_KERNEL_FFT_Y_FWD}, {16, 8}},
                              {&P->nt_z, {SPG_KERNEL_FFT_Z_WEIGHT}, {16, 8}}};
   if (P->fused) knobs.push_back({&fused, {SPG_KERNEL_PROX_TV, SPG_KERNEL_C2R_X, SPG_KERNEL_R2C_X}, {1, 0}});
-  knobs.push_back({&P->zc, {SPG_KERNEL_PROX_TV}, {32, 16, 64, 128, 256, 8, 4}});
+  knobs.push_back({&zsel, {SPG_KERNEL_PROX_TV}, {32, 16, 64, 128, 256, 8, 4}});
   // Each candidate is timed twice, in two sweeps over the candidates, and keeps the faster of
   // its two times, so that one slow sample on a busy GPU does not decide.  A pass may be
   // launched as several column ranges: the event capacity covers four launches per class
   // and iteration.
   for (Knob& kb : knobs) {
+    const bool depth = kb.val == &zsel;
+    if (depth && own && fused) kb.cand.push_back(0);
     std::vector<double> t_min(kb.cand.size(), 1e300);
     std::vector<bool> ran(kb.cand.size(), false);
     for (int sweep = 0; sweep < 2; ++sweep) {
       for (size_t ci = 0; ci < kb.cand.size(); ++ci) {
         *kb.val = kb.cand[ci];
         P->fused = fused != 0;
+        set_depth();
         if ((s = spg_set_map(P, nullptr))) return s;
         // warm, and past the first two iterations of a round (zero momentum: x_{k-1} unread)
         if ((s = spg_run(P, 3, nullptr))) return s;
@@ -1093,8 +1104,17 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
         best_ms = t_min[ci];
         best = kb.cand[ci];
       }
+    if (depth) {  // the depth to report: the best that is not the path's own
+      double zms = 1e300;
+      for (size_t ci = 0; ci < kb.cand.size(); ++ci)
+        if (ran[ci] && kb.cand[ci] != 0 && t_min[ci] < zms) {
+          zms = t_min[ci];
+          P->zc = kb.cand[ci];
+        }
+    }
     *kb.val = best;
     P->fused = fused != 0;
+    set_depth();
   }
   return spg_set_map(P, nullptr);
 }

@@ -64,7 +64,7 @@ int prox_num_blocks(const Dims& d, int zc);
 bool prox_fft_supported(const Dims& d);
 // Whether the kernel takes this grid and storage: those, and nx = 160 but for bf16 storage.
 bool prox_fft_runs(const Dims& d, int store);
-int prox_fft_slab(const Dims& d);  // a slab depth for it
+int prox_fft_slab(const Dims& d);  // the slab depth that suits it
 int prox_fft_num_blocks(const Dims& d, int zc);
 // mon: also the per-block partials of the objective's penalty terms at y_k (3 x nblocks
 // into a.partials)

@@ -3701,13 +3701,18 @@ bool prox_fft_runs(const Dims& d, int store) {
   return prox_fft_supported(d) || (d.nx == 160 && d.ny % PF_TY == 0 && (store == ST_PLAIN || store == ST_COMP));
 }
 
-// The most slabs that leave at most two blocks per CU at once, a third round of blocks being
-// as long as the first (160^3, 40 tiles: 10 to 12 slabs 86-94 us per iteration, 13 and more
-// 94-102, 8 and fewer 95 and up).
+// The shallowest slabs whose blocks all run at once: a block marches its planes one after the
+// other, 1.6 us each when it has a CU's SIMDs to itself, so depth is time until the chip is
+// full, and past that a further round of blocks costs as much as the first.  At once: four
+// blocks per CU up to 128 columns (256 threads, 40 KB LDS), two at 160 and 256, one at 512.
+// us per iteration by depth, compensated: 32^3 1: 13.9, 2: 14.9, 4: 16.9; 64^3 1: 27.2,
+// 4: 29.2; 8 x 32 x 256 1: 12.8, 4: 18.7; 128^3 2: 49.5, 4: 44.9, 8: 48.1, 16: 56; 160^3
+// 13 (520 blocks): 99, 16: 86, 20: 94; 512^3 stencil kernel 32: 850 us, 256: 775.
 int prox_fft_slab(const Dims& d) {
-  const int slabs = 512 / (d.ny / PF_TY) > 1 ? 512 / (d.ny / PF_TY) : 1;
-  const int zc = (d.nz + slabs - 1) / slabs;
-  return zc < 4 ? 4 : zc;
+  const int most = d.nx >= 512 ? 256 : (d.nx > 128 ? 512 : 1024);
+  const int tiles = d.ny / PF_TY;
+  const int slabs = most / tiles > 1 ? most / tiles : 1;
+  return (d.nz + slabs - 1) / slabs;
 }
 
 int prox_fft_num_blocks(const Dims& d, int zc) { return (d.ny / PF_TY) * ((d.nz + zc - 1) / zc); }
