@@ -219,9 +219,9 @@ spg_status spg_set_state(spg_problem* P, const void* d_buf, size_t bytes);
  * weights as set, with HIP events, each candidate twice (two sweeps, the faster time
  * counts), and keeps the fastest; it leaves the map at 0 with the momentum restarted.
  * Defaults: 16, 16 and a slab depth of 32 planes, halved (down to 4) while the stencil
- * kernel would run fewer than 512 blocks (small maps); the fused path (see spg_set_fusion)
- * picks a slab depth of its own, not reported here, until spg_set_launch_shape is called, and
- * the autotuner keeps that one where it measures fastest.  Results are bitwise independent of
+ * kernel would run fewer than 512 blocks (small maps); until
+ * spg_set_launch_shape is called the iterations pick a slab depth of their own, not reported
+ * here, and the autotuner keeps that one where it measures fastest.  Results are bitwise independent of
  * the launch shape. */
 spg_status spg_set_launch_shape(spg_problem* P, int32_t nt_y, int32_t nt_z, int32_t zc);
 spg_status spg_get_launch_shape(const spg_problem* P, int32_t* nt_y, int32_t* nt_z, int32_t* zc);

@@ -158,7 +158,7 @@ struct spg_problem {
   // launch shapes (chosen by spg_autotune): columns per tile of the y and z passes, z-slab
   // depth of the stencil kernel
   int nt_y = 16, nt_z = 16, zc = PT_ZC;
-  int zc_own = 0;  // the fused path's own slab depth while no launch shape has been set (0: zc)
+  bool zc_own = true;  // the iterations pick their own slab depth (until a launch shape is set), not zc
   bool fused = false;  // fused x-axis transforms in the stencil/prox kernel
   bool shared_gpu = false;  // being captured into a batch graph with other problems
   // unrolled solve recorded by spg_run_checkpointed for spg_vjp
@@ -433,9 +433,7 @@ spg_status spg_create(const spg_params* p, void* d_workspace, size_t bytes, void
   P->store = P->comp ? ST_COMP : ((p->flags & SPG_FLAG_BF16_STORAGE) ? ST_BF16 : ST_PLAIN);
   P->dn2 = dnorm2_of(p->nx, p->ny, p->nz);
   P->fused = prox_fft_runs(P->d, P->store);
-  if (P->fused) P->zc_own = prox_fft_slab(P->d);
-  // nominal z-slab depth of the stencil kernel, and the separate path's: 32 planes, or fewer on
-  // small maps, whose blocks (ny / 4 tiles per slab) would otherwise be too few to keep more
+  // nominal z-slab depth of the stencil kernels: 32 planes, or fewer on small maps, whose blocks (ny / 4 tiles per slab) would otherwise be too few to keep more
   // than a few CUs busy and each march through many planes in turn
   while (P->zc > 4 && (long long)(p->ny / 4) * ((p->nz + P->zc - 1) / P->zc) < 512) P->zc /= 2;
   P->mon_every = (p->flags & SPG_FLAG_MONITOR) ? p->obj_every : 0;
@@ -586,7 +584,7 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
     const double m_next = P->prm.accel ? (P->t - 1.0) / t_next : 0.0;
     const int nxt = 3 - P->cur - P->old;
     ProxArgs a = prox_args(P, nxt, P->m_cur, m_next);
-    if (fuse && P->zc_own) a.zc = P->zc_own;
+    if (P->zc_own) a.zc = fuse ? prox_fft_slab(d) : prox_tv_slab(d);
     if (capture_g) a.gsrc = capture_g;
     if (mon) {
       // 3 partials per block in region C (<= 3 x 65536; the slab depth does not change results)
@@ -1007,7 +1005,7 @@ spg_status spg_set_launch_shape(spg_problem* P, int32_t nt_y, int32_t nt_z, int3
   P->nt_y = nt_y;
   P->nt_z = nt_z;
   P->zc = zc;
-  P->zc_own = 0;
+  P->zc_own = false;
   return SPG_OK;
 }
 
@@ -1050,26 +1048,24 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
     std::vector<int> cand;
   };
   int fused = P->fused ? 1 : 0;
-  // the slab depth of the fused path may also stay the one it picks itself (candidate 0): then
-  // the depth that is reported is the best of the others
-  const int own = P->fused ? prox_fft_slab(P->d) : 0;
-  int zsel = own ? 0 : P->zc;
+  // the slab depth may also stay the one that the path picks itself (candidate 0): then the
+  // depth that is reported is the best of the others
+  int zsel = 0;
   auto set_depth = [&]() {
-    P->zc_own = zsel == 0 ? own : 0;
+    P->zc_own = zsel == 0;
     if (zsel) P->zc = zsel;
   };
   set_depth();
   std::vector<Knob> knobs = {{&P->nt_y, {SPG_KERNEL_FFT_Y_FWD}, {16, 8}},
                              {&P->nt_z, {SPG_KERNEL_FFT_Z_WEIGHT}, {16, 8}}};
   if (P->fused) knobs.push_back({&fused, {SPG_KERNEL_PROX_TV, SPG_KERNEL_C2R_X, SPG_KERNEL_R2C_X}, {1, 0}});
-  knobs.push_back({&zsel, {SPG_KERNEL_PROX_TV}, {32, 16, 64, 128, 256, 8, 4}});
+  knobs.push_back({&zsel, {SPG_KERNEL_PROX_TV}, {32, 16, 64, 128, 256, 8, 4, 0}});
   // Each candidate is timed twice, in two sweeps over the candidates, and keeps the faster of
   // its two times, so that one slow sample on a busy GPU does not decide.  A pass may be
   // launched as several column ranges: the event capacity covers four launches per class
   // and iteration.
   for (Knob& kb : knobs) {
     const bool depth = kb.val == &zsel;
-    if (depth && own && fused) kb.cand.push_back(0);
     std::vector<double> t_min(kb.cand.size(), 1e300);
     std::vector<bool> ran(kb.cand.size(), false);
     for (int sweep = 0; sweep < 2; ++sweep) {
@@ -1127,8 +1123,8 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
 // arguments: buffers, momenta, step, shapes, paths), and the part of it that advances.
 struct IterSig {
   spg_params prm;
-  int store, cur, old, nt_y, nt_z, zc, zc_own;
-  bool prior_set, primed, unif_u, unif_v, fused;
+  int store, cur, old, nt_y, nt_z, zc;
+  bool zc_own, prior_set, primed, unif_u, unif_v, fused;
   double lr, t, m_cur;
   int32_t j;
   int64_t hist_n;  // a graph with monitored iterations writes fixed history slots

@@ -56,6 +56,7 @@ struct ProxArgs {
 };
 
 int prox_num_blocks(const Dims& d, int zc);
+int prox_tv_slab(const Dims& d);  // the slab depth that suits the separate path's kernel
 
 // Fused x-axis transforms + stencil/prox on full-width rows: reads the gradient as the
 // packed x-spectrum rows in S (after the y and z passes), writes x_{k+1} and the

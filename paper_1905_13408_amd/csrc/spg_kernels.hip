@@ -3662,6 +3662,16 @@ int prox_num_blocks(const Dims& d, int zc) {
   return ntx * nty * ntz;
 }
 
+// As prox_fft_slab: the shallowest slabs whose blocks (256 threads, four per CU) all run at
+// once.  us per iteration by depth, 192^3 (72 tiles) compensated 8: 127, 14 (1008 blocks): 125,
+// 16: 130, 32: 141; 160^3 bf16 (60 tiles) 8: 106, 10: 97, 16: 106; 192 x 192 x 64 4: 63, 6: 60,
+// 16: 71.
+int prox_tv_slab(const Dims& d) {
+  const int tiles = ((d.nx + PT_TX - 1) / PT_TX) * ((d.ny + PT_TY - 1) / PT_TY);
+  const int slabs = 1024 / tiles > 1 ? 1024 / tiles : 1;
+  return (d.nz + slabs - 1) / slabs;
+}
+
 hipError_t launch_prox_tv(const Dims& d, const ProxArgs& a, int store, bool check, hipStream_t st, bool mon) {
   const int ntx = (d.nx + PT_TX - 1) / PT_TX;
   const int nty = (d.ny + PT_TY - 1) / PT_TY;
