@@ -2431,7 +2431,8 @@ __global__ void __launch_bounds__(256) k_fold(Dims d, const float* __restrict__ 
 // of lambda and mu.
 // A row (kz, ky) is taken together with its mirror row (-kz, -ky), whose columns run
 // backwards, so that every element is read once: both k and -k are at hand for h, and
-// |h(k)| = |h(-k)| (read once per element and once as a mirror: 911 us at 512^3, 594 now).
+// |h(k)| = |h(-k)| (read once per element and once as a mirror: 911 us at 512^3; 594-642 on
+// 1024 blocks, 460 on 2048: bound by the loads in flight).
 __global__ void __launch_bounds__(256) k_data_stats(Dims d, const float* __restrict__ w,
                                                     const float2* __restrict__ b, double* __restrict__ partials) {
   __shared__ double s_red[8];
