@@ -3191,7 +3191,7 @@ __global__ void __launch_bounds__(BP_NT) k_bp_tiles(Dims d, int n_img, int m, co
   __shared__ int4 s_item[BP_NT];          // image << 6 | copy, first u, first v, extents
   __shared__ uint2 s_queue[BP_QUEUE];     // image << 6 | copy, (u, v)
   __shared__ int s_n[4];                  // copies, items, queued pixels, waves with items left
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // tile of this block: axis order 0, last, 1, last - 1, ... puts the tiles around k = 0
   // first; the order along x is rotated from row to row, or each of the 8 XCDs, which take
   // blocks in turn, would get the same few x all over and two of them most of the work
@@ -3357,11 +3357,14 @@ __global__ void __launch_bounds__(BP_NT) k_bp_tiles(Dims d, int n_img, int m, co
       }
     }
     __syncthreads();
-    const int items = s_n[1];
+    const int items = __builtin_amdgcn_readfirstlane(s_n[1]);
     int it = wave, c0 = 0;  // this wave's place in the list of hits
     for (;;) {
-      // ---- queue the pixels of the hits, until every wave is done or the queue is nearly full
-      while (it < items && *(volatile int*)&s_n[2] <= BP_QUEUE - 64 * NWAVE) {
+      // ---- queue the pixels of the hits, until every wave is done or the queue is nearly full:
+      // one decision per wave, from one lane's read (the other waves add to the word meanwhile,
+      // so that two lanes may read two values).  A wave adds at most 64 pixels to a queue that
+      // had room for one such step of every wave.
+      while (it < items && __builtin_amdgcn_readfirstlane(*(volatile int*)&s_n[2]) <= BP_QUEUE - 64 * NWAVE) {
         const int4 item = s_item[it];
         const unsigned key = (unsigned)__builtin_amdgcn_readfirstlane(item.x);
         const int ext = __builtin_amdgcn_readfirstlane(item.w);
