@@ -298,7 +298,8 @@ spg_status spg_vjp(spg_problem* P, void* d_vjp_ws, size_t bytes, const float* d_
  * d_images: n_img*m*m complex; d_rot: n_img row-major 3x3 double matrices; d_ctf: n_img*m*m
  * float or NULL (1); d_weight: n_img posterior weights or NULL (1).  Device pointers; the
  * workspace (spg_backproject_workspace_size bytes, 8-byte aligned) holds the accumulators;
- * asynchronous on hip_stream.  The sums are int64 fixed point with a power-of-two scale per
+ * asynchronous on hip_stream.  The outputs may overlay the inputs (the call then takes the
+ * slower path of atomic sums in memory).  The sums are int64 fixed point with a power-of-two scale per
  * component (chosen from the largest term and the pixel count so that no sum can overflow;
  * terms are rounded at 2^-62 of that bound), so results are bitwise reproducible and do not
  * depend on the order of the images. */

@@ -3928,6 +3928,12 @@ hipError_t launch_expand_bbar(const Dims& d, const float2* S, const float* w, fl
   return hipGetLastError();
 }
 
+// Whether the ranges of bytes share any.
+static bool bp_overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + nb && y < x + na;
+}
+
 // Tiles where every axis has at least 16 points (below, tiles are few and mostly halo), a
 // tile has at most 4 copies per axis within reach (m <= 2 n), image and copy fit the 31 bits
 // of a queue entry, 1 / h is finite, and the workspace holds the flag word (it is rounded up
@@ -3944,7 +3950,14 @@ hipError_t launch_backproject(const Dims& d, int n_img, int m, const float2* ima
   // matrix is not a rotation
   unsigned long long* acc = static_cast<unsigned long long*>(ws);
   unsigned long long* mx = acc + 3 * d.nvox;
-  const bool tiled = bp_tiled(d, n_img, m, h, bytes);
+  // the tiles' blocks write w and b while others still read the inputs, so outputs that overlay
+  // an input (or the sums) take the general path, which writes them after its last read
+  const size_t pix = (size_t)n_img * m * m, img = (size_t)n_img, nv = (size_t)d.nvox;
+  auto overlaid = [&](const void* out, size_t n) {
+    return bp_overlap(out, n, images, pix * 8) || bp_overlap(out, n, rots, img * 72) ||
+           bp_overlap(out, n, ctf, pix * 4) || bp_overlap(out, n, weights, img * 4) || bp_overlap(out, n, ws, bytes);
+  };
+  const bool tiled = bp_tiled(d, n_img, m, h, bytes) && !overlaid(w, nv * 4) && !overlaid(b, nv * 8);
   unsigned long long* other = tiled ? mx + 3 : nullptr;
   hipError_t e;
   if (tiled) k_fill_f64<<<1, 64, 0, st>>>(reinterpret_cast<double*>(mx), 4, nullptr);
