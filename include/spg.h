@@ -237,9 +237,11 @@ spg_status spg_autotune(spg_problem* P, int32_t iters);
  * SPG_FLAG_BF16_STORAGE the fused path keeps the gradient and extrapolated rows in fp32.
  * spg_set_fusion(P, 1) on a grid without support returns SPG_E_UNSUPPORTED; 0 selects
  * the separate sweeps, which spg_autotune then keeps (it may turn the fused path off where
- * the separate sweeps measure faster, never on).  On nx = 160 the library picks the path
- * itself (fused but with SPG_FLAG_BF16_STORAGE): spg_get_fusion reports 0 there and
- * spg_set_fusion(P, 0) changes nothing.  Iterations of spg_run_checkpointed and the
+ * the separate sweeps measure faster, never on).  On nx = 160
+ * the two paths give the same bits, so there is nothing to choose but time: spg_get_fusion
+ * reports 0 and spg_set_fusion(P, 1) refuses, as on the other widths without support, but the
+ * fused kernel runs (except with SPG_FLAG_BF16_STORAGE) until spg_set_fusion(P, 0) selects the
+ * separate sweeps or spg_autotune measures them faster.  Iterations of spg_run_checkpointed and the
  * replays of spg_vjp always use the separate sweeps (the replays keep the data gradient of
  * every iteration), so that the recorded and replayed trajectories agree bitwise; the
  * setting is restored afterwards. */

@@ -1018,13 +1018,14 @@ spg_status spg_set_fusion(spg_problem* P, int32_t enable) {
   spg_status s = usable(P);
   if (s) return s;
   if (enable && !prox_fft_supported(P->d))
-    return set_err(P, SPG_E_UNSUPPORTED, "fused x transforms need nx in {64, 128, 256, 512} and ny % 4 == 0");
-  if (prox_fft_supported(P->d)) P->fused = enable != 0;  // else the path is not the caller's to choose
+    return set_err(P, SPG_E_UNSUPPORTED, "fused x transforms need nx in {32, 64, 128, 256, 512} and ny % 4 == 0");
+  P->fused = enable != 0;
   return SPG_OK;
 }
 
 spg_status spg_get_fusion(const spg_problem* P, int32_t* enabled) {
   if (!P || !enabled) return SPG_E_INVAL;
+  // the choice between two roundings; 160 columns have one (see prox_fft_runs)
   *enabled = P->fused && prox_fft_supported(P->d) ? 1 : 0;
   return SPG_OK;
 }

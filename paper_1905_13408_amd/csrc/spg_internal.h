@@ -63,7 +63,8 @@ int prox_tv_slab(const Dims& d);  // the slab depth that suits the separate path
 // x-spectrum of y_{k+1} back into S.  Grids with nx in {32, 64, 128, 256, 512} and ny a
 // multiple of 4 (the kernel's tile height).
 bool prox_fft_supported(const Dims& d);
-// Whether the kernel takes this grid and storage: those, and nx = 160 but for bf16 storage.
+// Whether the kernel takes this grid and storage: those, and nx = 160 but for bf16 storage, where
+// its iterates are bitwise those of the separate sweeps.
 bool prox_fft_runs(const Dims& d, int store);
 int prox_fft_slab(const Dims& d);  // the slab depth that suits it
 int prox_fft_num_blocks(const Dims& d, int zc);

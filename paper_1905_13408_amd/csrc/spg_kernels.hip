@@ -1735,6 +1735,20 @@ struct PfT {  // threads per row of the M-point complex transforms
   static constexpr int E = M / T;
 };
 
+// sc Dy of the TV gradient.  On 160 columns, where the caller does not choose between this
+// kernel and the separate sweeps, the product is rounded by itself, as k_prox_tv stores it, so
+// that the two give the same bits (the transforms do); elsewhere the compiler may fuse it into
+// the sum that follows, and the two agree to that rounding.
+template <int NX>
+__device__ __forceinline__ float tv_term(float sc, float dy) {
+  if constexpr (mixed_len(NX)) {
+#pragma clang fp contract(off)
+    return sc * dy;
+  } else {
+    return __fmul_rn(sc, dy);
+  }
+}
+
 // PRIOR: the gamma term's previous map is given (else it is 0).  NT: x_{k+1} and the
 // spectrum rows go out by streaming stores (maps whose spectrum outgrows the last-level
 // cache; smaller maps are read back by the next pass while still cached).  MON: also the
@@ -2024,13 +2038,13 @@ __global__ void __launch_bounds__(2 * NX) k_prox_fft(ProxArgs a, float2* __restr
         const int ly = r + 2 * h;
         const float yc = Y0[ly + 1][x];
         const float sc = SC0[ly][x];
-        // p = sc Dy rounded as stored fp32 values, summed in the order z, y, x, -x+, -y+, -z+
-        const float pzc = __fmul_rn(sc, yc - Ym[ly + 1][x]);
-        const float pyc = __fmul_rn(sc, yc - Y0[ly][x]);
-        const float pxc = __fmul_rn(sc, yc - Y0[ly + 1][xm]);
-        const float pxn = __fmul_rn(SC0[ly][xp], Y0[ly + 1][xp] - yc);
-        const float pyn = __fmul_rn(SC0[ly + 1][x], Y0[ly + 2][x] - yc);
-        const float pzn = __fmul_rn(sc1[h], Y1[ly + 1][x] - yc);
+        // p = sc Dy, summed in the order z, y, x, -x+, -y+, -z+
+        const float pzc = tv_term<NX>(sc, yc - Ym[ly + 1][x]);
+        const float pyc = tv_term<NX>(sc, yc - Y0[ly][x]);
+        const float pxc = tv_term<NX>(sc, yc - Y0[ly + 1][xm]);
+        const float pxn = tv_term<NX>(SC0[ly][xp], Y0[ly + 1][xp] - yc);
+        const float pyn = tv_term<NX>(SC0[ly + 1][x], Y0[ly + 2][x] - yc);
+        const float pzn = tv_term<NX>(sc1[h], Y1[ly + 1][x] - yc);
         const float gtv = pzc + pyc + pxc - pxn - pyn - pzn;
         const float gd = G[ly][x];
         const float uu = widen(u_cur[h]);

@@ -324,13 +324,15 @@ class SPGSolver:
 
     @property
     def fusion(self) -> bool:
-        """Whether iterations run the x-axis transforms inside the stencil/prox kernel."""
+        """Whether the fused x-transform path is selected, on the grids that offer the choice (False
+        on the others; 160 columns run fused with the bits of the separate sweeps)."""
         v = c_int32()
         self._check(self._L.spg_get_fusion(self._h, byref(v)))
         return bool(v.value)
 
     def set_fusion(self, enable: bool):
-        """Select the fused x-transform path (raises where the grid has no support)."""
+        """Select the fused x-transform path (raises where the grid does not offer it) or, with
+        False, the separate sweeps."""
         self._check(self._L.spg_set_fusion(self._h, 1 if enable else 0))
 
     # ------------------------------------------------------------------ reverse mode
