@@ -218,11 +218,11 @@ spg_status spg_set_state(spg_problem* P, const void* d_buf, size_t bytes);
  * untimed ones, so that the momentum term is active) from the zero map, with the penalty
  * weights as set, with HIP events, each candidate twice (two sweeps, the faster time
  * counts), and keeps the fastest; it leaves the map at 0 with the momentum restarted.
- * Defaults: 16, 16 and a slab depth of 32 planes, halved (down to 4) while the stencil
- * kernel would run fewer than 512 blocks (small maps); until
- * spg_set_launch_shape is called the iterations pick a slab depth of their own, not reported
- * here, and the autotuner keeps that one where it measures fastest.  Results are bitwise independent of
- * the launch shape. */
+ * Defaults: 16, 16 and the depth at which the stencil kernel's blocks all run at once, which
+ * the autotuner tries too.  spg_get_launch_shape reports what runs, and setting what it reports
+ * (with the fusion setting) gives the same launches again: a depth of 4, the least that can
+ * be set, stands for 4 planes or the fewer at which the blocks of a small map run at once.
+ * Results are bitwise independent of the launch shape. */
 spg_status spg_set_launch_shape(spg_problem* P, int32_t nt_y, int32_t nt_z, int32_t zc);
 spg_status spg_get_launch_shape(const spg_problem* P, int32_t* nt_y, int32_t* nt_z, int32_t* zc);
 spg_status spg_autotune(spg_problem* P, int32_t iters);

@@ -162,7 +162,7 @@ struct spg_problem {
   // launch shapes (chosen by spg_autotune): columns per tile of the y and z passes, z-slab
   // depth of the stencil kernel
   int nt_y = 16, nt_z = 16, zc = PT_ZC;
-  bool zc_own = true;  // the iterations pick their own slab depth (until a launch shape is set), not zc
+  bool zc_own = true;  // no launch shape set or tuned: the path's own slab depth in place of zc
   bool fused = false;  // fused x-axis transforms in the stencil/prox kernel
   bool shared_gpu = false;  // being captured into a batch graph with other problems
   // unrolled solve recorded by spg_run_checkpointed for spg_vjp
@@ -566,6 +566,17 @@ spg_status spg_set_map(spg_problem* P, const float* d_x0) {
   return SPG_OK;
 }
 
+// Slab depth of the iterations.  The shallowest depth that can be set, 4, leaves it to the path
+// to go shallower still (one plane on the smallest maps), so that every depth in use has a
+// number that sets it again.
+constexpr int kMinDepth = 4;
+static int own_depth(const spg_problem* P, bool fuse) { return fuse ? prox_fft_slab(P->d) : prox_tv_slab(P->d); }
+static int slab_depth(const spg_problem* P, bool fuse) {
+  const int own = own_depth(P, fuse);
+  if (P->zc_own) return own;
+  return P->zc > kMinDepth ? P->zc : std::min(kMinDepth, own);
+}
+
 // One SPG iteration; with capture_g, the data gradient of y_k is left there (fp32).
 static spg_status iterate_once(spg_problem* P, float* capture_g) {
   spg_status s;
@@ -589,7 +600,7 @@ static spg_status iterate_once(spg_problem* P, float* capture_g) {
     const double m_next = P->prm.accel ? (P->t - 1.0) / t_next : 0.0;
     const int nxt = 3 - P->cur - P->old;
     ProxArgs a = prox_args(P, nxt, P->m_cur, m_next);
-    if (P->zc_own) a.zc = fuse ? prox_fft_slab(d) : prox_tv_slab(d);
+    a.zc = slab_depth(P, fuse);
     if (capture_g) a.gsrc = capture_g;
     if (mon) {
       // 3 partials per block in region C (<= 3 x 65536; the slab depth does not change results)
@@ -1005,7 +1016,7 @@ extern "C" {
 spg_status spg_set_launch_shape(spg_problem* P, int32_t nt_y, int32_t nt_z, int32_t zc) {
   spg_status s = usable(P);
   if (s) return s;
-  if ((nt_y != 8 && nt_y != 16) || (nt_z != 8 && nt_z != 16) || zc < 4 || zc > 512)
+  if ((nt_y != 8 && nt_y != 16) || (nt_z != 8 && nt_z != 16) || zc < kMinDepth || zc > 512)
     return set_err(P, SPG_E_INVAL, "nt_y, nt_z must be 8 or 16 and zc in [4, 512]");
   P->nt_y = nt_y;
   P->nt_z = nt_z;
@@ -1034,7 +1045,7 @@ spg_status spg_get_launch_shape(const spg_problem* P, int32_t* nt_y, int32_t* nt
   if (!P) return SPG_E_INVAL;
   if (nt_y) *nt_y = P->nt_y;
   if (nt_z) *nt_z = P->nt_z;
-  if (zc) *zc = P->zc;
+  if (zc) *zc = P->zc_own ? std::max(kMinDepth, own_depth(P, P->fused)) : P->zc;
   return SPG_OK;
 }
 
@@ -1054,31 +1065,26 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
     std::vector<int> cand;
   };
   int fused = P->fused ? 1 : 0;
-  // the slab depth may also stay the one that the path picks itself (candidate 0): then the
-  // depth that is reported is the best of the others
-  int zsel = 0;
-  auto set_depth = [&]() {
-    P->zc_own = zsel == 0;
-    if (zsel) P->zc = zsel;
-  };
-  set_depth();
   std::vector<Knob> knobs = {{&P->nt_y, {SPG_KERNEL_FFT_Y_FWD}, {16, 8}},
                              {&P->nt_z, {SPG_KERNEL_FFT_Z_WEIGHT}, {16, 8}}};
   if (P->fused) knobs.push_back({&fused, {SPG_KERNEL_PROX_TV, SPG_KERNEL_C2R_X, SPG_KERNEL_R2C_X}, {1, 0}});
-  knobs.push_back({&zsel, {SPG_KERNEL_PROX_TV}, {32, 16, 64, 128, 256, 8, 4, 0}});
+  knobs.push_back({&P->zc, {SPG_KERNEL_PROX_TV}, {32, 16, 64, 128, 256, 8, 4}});
   // Each candidate is timed twice, in two sweeps over the candidates, and keeps the faster of
   // its two times, so that one slow sample on a busy GPU does not decide.  A pass may be
   // launched as several column ranges: the event capacity covers four launches per class
   // and iteration.
   for (Knob& kb : knobs) {
-    const bool depth = kb.val == &zsel;
+    if (kb.val == &P->zc) {  // the depths to try: those and the path's own
+      const int own = std::max(kMinDepth, own_depth(P, P->fused));
+      if (std::find(kb.cand.begin(), kb.cand.end(), own) == kb.cand.end()) kb.cand.push_back(own);
+      P->zc_own = false;
+    }
     std::vector<double> t_min(kb.cand.size(), 1e300);
     std::vector<bool> ran(kb.cand.size(), false);
     for (int sweep = 0; sweep < 2; ++sweep) {
       for (size_t ci = 0; ci < kb.cand.size(); ++ci) {
         *kb.val = kb.cand[ci];
         P->fused = fused != 0;
-        set_depth();
         if ((s = spg_set_map(P, nullptr))) return s;
         // warm, and past the first two iterations of a round (zero momentum: x_{k-1} unread)
         if ((s = spg_run(P, 3, nullptr))) return s;
@@ -1106,17 +1112,8 @@ spg_status spg_autotune(spg_problem* P, int32_t iters) {
         best_ms = t_min[ci];
         best = kb.cand[ci];
       }
-    if (depth) {  // the depth to report: the best that is not the path's own
-      double zms = 1e300;
-      for (size_t ci = 0; ci < kb.cand.size(); ++ci)
-        if (ran[ci] && kb.cand[ci] != 0 && t_min[ci] < zms) {
-          zms = t_min[ci];
-          P->zc = kb.cand[ci];
-        }
-    }
     *kb.val = best;
     P->fused = fused != 0;
-    set_depth();
   }
   return spg_set_map(P, nullptr);
 }
