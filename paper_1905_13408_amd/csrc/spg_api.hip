@@ -163,6 +163,7 @@ struct spg_problem {
   // depth of the stencil kernel
   int nt_y = 16, nt_z = 16, zc = PT_ZC;
   bool zc_own = true;  // no launch shape set or tuned: the path's own slab depth in place of zc
+  int cus = 256;  // CUs of the device, once it is used
   bool fused = false;  // fused x-axis transforms in the stencil/prox kernel
   bool shared_gpu = false;  // being captured into a batch graph with other problems
   // unrolled solve recorded by spg_run_checkpointed for spg_vjp
@@ -236,6 +237,7 @@ spg_status device_init(spg_problem* P) {
     SPG_CK(P, hipStreamSynchronize(P->stream));
   }
   SPG_CK(P, launch_set_map(P->d, nullptr, P->xhi(P->cur), P->xlo(P->cur), P->stream));
+  P->cus = cu_count();
   restart(P);
   P->dev_ready = true;
   return SPG_OK;
@@ -570,7 +572,9 @@ spg_status spg_set_map(spg_problem* P, const float* d_x0) {
 // to go shallower still (one plane on the smallest maps), so that every depth in use has a
 // number that sets it again.
 constexpr int kMinDepth = 4;
-static int own_depth(const spg_problem* P, bool fuse) { return fuse ? prox_fft_slab(P->d) : prox_tv_slab(P->d); }
+static int own_depth(const spg_problem* P, bool fuse) {
+  return fuse ? prox_fft_slab(P->d, P->cus) : prox_tv_slab(P->d, P->store, P->cus);
+}
 static int slab_depth(const spg_problem* P, bool fuse) {
   const int own = own_depth(P, fuse);
   if (P->zc_own) return own;

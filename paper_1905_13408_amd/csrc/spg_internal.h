@@ -56,7 +56,8 @@ struct ProxArgs {
 };
 
 int prox_num_blocks(const Dims& d, int zc);
-int prox_tv_slab(const Dims& d);  // the slab depth that suits the separate path's kernel
+int cu_count();  // of the current device
+int prox_tv_slab(const Dims& d, int store, int cus);  // the slab depth that suits the separate path's kernel
 
 // Fused x-axis transforms + stencil/prox on full-width rows: reads the gradient as the
 // packed x-spectrum rows in S (after the y and z passes), writes x_{k+1} and the
@@ -66,7 +67,7 @@ bool prox_fft_supported(const Dims& d);
 // Whether the kernel takes this grid and storage: those, and nx = 160 but for bf16 storage, where
 // its iterates are bitwise those of the separate sweeps.
 bool prox_fft_runs(const Dims& d, int store);
-int prox_fft_slab(const Dims& d);  // the slab depth that suits it
+int prox_fft_slab(const Dims& d, int cus);  // the slab depth that suits it
 int prox_fft_num_blocks(const Dims& d, int zc);
 // mon: also the per-block partials of the objective's penalty terms at y_k (3 x nblocks
 // into a.partials)

@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "spg_internal.h"
@@ -3517,7 +3518,7 @@ __global__ void __launch_bounds__(256) k_obj_finish(const double* __restrict__ p
     default: return hipErrorInvalidValue;              \
   }
 
-static int cu_count() {
+int cu_count() {
   int dev = 0, n = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       n < 1)
@@ -3721,14 +3722,18 @@ int prox_num_blocks(const Dims& d, int zc) {
   return ntx * nty * ntz;
 }
 
-// As prox_fft_slab: the shallowest slabs whose blocks (256 threads, four per CU) all run at
-// once.  us per iteration by depth, 192^3 (72 tiles) compensated 8: 127, 14 (1008 blocks): 125,
-// 16: 130, 32: 141; 160^3 bf16 (60 tiles) 8: 106, 10: 97, 16: 106; 192 x 192 x 64 4: 63, 6: 60,
-// 16: 71.
-int prox_tv_slab(const Dims& d) {
+// As prox_fft_slab: the shallowest slabs whose blocks (256 threads, four per CU in every
+// storage mode) all run at once.  us per iteration by depth, 192^3 (72 tiles) compensated 8: 127,
+// 14 (1008 blocks): 125, 16: 130, 32: 141; 160^3 bf16 (60 tiles) 8: 106, 10: 97, 16: 106; 192 x 192
+// x 64 4: 63, 6: 60, 16: 71.  Compensated, deep slabs cost more than the rounds of blocks they
+// save: 512^3 32: 2004, 64: 2022, 256 (one round): 2149; 256 x 512 x 512 32: 1046, 128: 1071; 512 x 512
+// x 192 32: 815, 103: 832; at 52 planes they are even (256 x 512 x 192: 399).  In fp32 and bf16
+// one round is as good at any depth (512^3 fp32 32: 1935, 256: 1935; bf16 1738, 1711).
+int prox_tv_slab(const Dims& d, int store, int cus) {
   const int tiles = ((d.nx + PT_TX - 1) / PT_TX) * ((d.ny + PT_TY - 1) / PT_TY);
-  const int slabs = 1024 / tiles > 1 ? 1024 / tiles : 1;
-  return (d.nz + slabs - 1) / slabs;
+  const int slabs = std::max(1, 4 * cus / tiles);
+  const int zc = (d.nz + slabs - 1) / slabs;
+  return store == ST_COMP && zc > 48 ? PT_ZC : zc;
 }
 
 hipError_t launch_prox_tv(const Dims& d, const ProxArgs& a, int store, bool check, hipStream_t st, bool mon) {
@@ -3772,16 +3777,24 @@ bool prox_fft_runs(const Dims& d, int store) {
 
 // The shallowest slabs whose blocks all run at once: a block marches its planes one after the
 // other, 1.6 us each when it has a CU's SIMDs to itself, so depth is time until the chip is
-// full, and past that a further round of blocks costs as much as the first.  At once: four
-// blocks per CU up to 128 columns (256 threads, 40 KB LDS), two at 160 and 256, one at 512.
+// full, and past that a further round of blocks costs as much as the first.  At once, by the 16
+// waves of 128 registers and the 160 KB of a CU (a block is 2 nx threads and 0.3 KB per column, in
+// every storage mode): 16 blocks at 32 columns, 8, 4, 2 at 256 and one at 512; two at 160.
 // us per iteration by depth, compensated: 32^3 1: 13.9, 2: 14.9, 4: 16.9; 64^3 1: 27.2,
 // 4: 29.2; 8 x 32 x 256 1: 12.8, 4: 18.7; 128^3 2: 49.5, 4: 44.9, 8: 48.1, 16: 56; 160^3
-// 13 (520 blocks): 99, 16: 86, 20: 94; 512^3 stencil kernel 32: 850 us, 256: 775.
-int prox_fft_slab(const Dims& d) {
-  const int most = d.nx >= 512 ? 256 : (d.nx > 128 ? 512 : 1024);
-  const int tiles = d.ny / PF_TY;
-  const int slabs = most / tiles > 1 ? most / tiles : 1;
-  return (d.nz + slabs - 1) / slabs;
+// 13 (520 blocks): 99, 16: 86, 20: 94; 512 x 512 x 32 8: 140, 16: 140, 32: 154, 64: 193; 512 x 512 x
+// 64 8: 240, 32: 240, 64: 262; 512^3 stencil kernel 32: 850, 256: 775.
+// Two exceptions.  Past four blocks per CU a plane's halo counts: slabs of fewer than 4 planes
+// are taken only as far as four blocks per CU ask for them (128 x 64 x 64 1: 25.9, 2: 24.8; 128 x 128 x
+// 32 1: 28.5, 4: 27.8).  And up to 128 columns slabs deeper than 48 planes are not worth one
+// round only: 512 x 512 x 128 32: 435, 64 (one round): 452.
+int prox_fft_slab(const Dims& d, int cus) {
+  auto depth = [&](int per_cu) {
+    const int slabs = std::max(1, per_cu * cus / (d.ny / PF_TY));
+    return (d.nz + slabs - 1) / slabs;
+  };
+  const int zc = std::max(depth(d.nx == 160 ? 2 : 512 / d.nx), std::min(4, depth(4)));
+  return d.nx <= 128 && zc > 48 ? PT_ZC : zc;
 }
 
 int prox_fft_num_blocks(const Dims& d, int zc) { return (d.ny / PF_TY) * ((d.nz + zc - 1) / zc); }
