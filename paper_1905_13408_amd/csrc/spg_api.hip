@@ -324,7 +324,7 @@ spg_status gradient_pipeline(spg_problem* P, bool obj, int* nA, void* gout, bool
                                 P->bf()));
       prof_end(P, SPG_KERNEL_FFT_Y_FWD);
       prof_begin(P, SPG_KERNEL_FFT_Z_WEIGHT);
-      // the objective variant writes one partial per block: 16-column tiles keep <= 8192 blocks
+      // the objective variant writes one partial per block, at most 4096 and 257 of the packed plane
       SPG_CK(P, launch_fft_cols(d, P->S(), 2, obj ? 3 : 2, twz, &fd, obj ? P->part() + kPartA : nullptr, st, nA,
                                 obj ? 16 : P->nt_z, !P->shared_gpu, kx0, nkx, P->bf()));
       prof_end(P, SPG_KERNEL_FFT_Z_WEIGHT);

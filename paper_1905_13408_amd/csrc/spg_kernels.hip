@@ -686,21 +686,30 @@ enum { ZP_PAIR, ZP_RIDE, ZP_APART };
 template <int L, int MODE>
 struct ZPlane {
   static constexpr int value = L < 256 || (L == 256 && MODE == 3) ? ZP_PAIR : (L == 256 ? ZP_RIDE : ZP_APART);
+  // Objective passes of more tiles than this leave the plane to k_dc_pairs_obj: with its fp64
+  // sums the paired pass needs 160 registers, and on long passes the third it loses of its waves
+  // costs more than the 16 us of another launch (z and plane, paired / apart, us: 256 x 512 x 512
+  // 255 / 211, 256 x 192 x 256 52 / 50, 256 x 160 x 256 43 / 45; 160 x 512 x 512 173 / 127, 160 x 192 x 192
+  // 32 / 30; 128 x 512 x 512 107 / 92, 128 x 256 x 256 28 / 31).  Not at 192 points, where the two
+  // round differently and monitored iterates would no longer be the unmonitored ones.
+  static constexpr int obj_apart = L == 256 ? 1280 : (L == 160 ? 1024 : (L == 128 ? 2048 : 1 << 30));
 };
 
-// ZP_RIDE: thread (c, q) holds column c & 1 of the block's pair c / 2, points q + T i.
-template <int L, bool DATA>
-__device__ __forceinline__ void dc_pairs(float2* __restrict__ S, int P, int ny, long long pstride,
+// Thread (c, q) holds column c & 1 of the block's pair c / 2, points q + T i.  Returns the thread's
+// terms of the objective (OBJ).
+template <int L, int T, bool DATA, bool OBJ>
+__device__ __forceinline__ double dc_pairs(float2* __restrict__ S, int P, int ny, long long pstride,
                                          const float2* __restrict__ tw, const float* __restrict__ ws,
                                          const float2* __restrict__ cs, const float* __restrict__ wnyq,
                                          const float2* __restrict__ cnyq, float* s_re, float* s_im, float2* s_tw,
                                          int NT, int c, int q) {
-  constexpr int T = ColT<L>::T;
   constexpr int E = RegPlan<L, T>::E;
+  double acc = 0.0;
   const int pair = (int)blockIdx.x * (NT >> 1) + (c >> 1);
   const int ky = min(pair, ny / 2);  // past the last pair: that one again, not stored
   const int kyp = ky == 0 ? 0 : ny - ky;
   const int myky = (c & 1) ? kyp : ky;
+  const bool own = pair <= ny / 2 && ((c & 1) == 0 || ky != kyp);  // each column once
   const int WG = P < 16 ? P : 16;
   float2* __restrict__ Sc = S + (long long)myky * P;
   float2 a[E];
@@ -735,23 +744,46 @@ __device__ __forceinline__ void dc_pairs(float2* __restrict__ S, int P, int ny, 
     const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
     const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
     const float2 B = make_float2(dd.y, -dd.x);
+    if constexpr (OBJ) {
+      if (own)
+        acc += 0.5 * (double)w0 * ((double)A.x * A.x + (double)A.y * A.y) - ((double)c0.x * A.x + (double)c0.y * A.y) +
+               0.5 * (double)wn * ((double)B.x * B.x + (double)B.y * B.y) - ((double)cn.x * B.x + (double)cn.y * B.y);
+    }
     const float2 g0 = make_float2(w0 * A.x - c0.x, w0 * A.y - c0.y);
     const float2 gn = make_float2(wn * B.x - cn.x, wn * B.y - cn.y);
     a[i] = make_float2(g0.x - gn.y, g0.y + gn.x);
   }
   __syncthreads();
   fft_reg<L, true, T>(a, re, im, NT, q, s_tw);
-  if (pair <= ny / 2 && ((c & 1) == 0 || ky != kyp)) {
+  if (own) {
 #pragma unroll
     for (int i = 0; i < E; ++i) Sc[(long long)(q + T * i) * pstride] = a[i];
   }
+  return acc;
+}
+
+// The plane's launch beside an objective pass that leaves it out: one pair per block.
+template <int L, int T>
+__global__ void __launch_bounds__(2 * T)
+    k_dc_pairs_obj(float2* __restrict__ S, int P, int ny, long long pstride, const float2* __restrict__ tw,
+                   const float* __restrict__ ws, const float2* __restrict__ cs, const float* __restrict__ wnyq,
+                   const float2* __restrict__ cnyq, double* __restrict__ partials) {
+  __shared__ float s_re[L * 2];
+  __shared__ float s_im[L * 2];
+  __shared__ float2 s_tw[L];
+  __shared__ double s_red[(2 * T + 63) / 64];
+  const double acc = dc_pairs<L, T, true, true>(S, P, ny, pstride, tw, ws, cs, wnyq, cnyq, s_re, s_im, s_tw, 2,
+                                                threadIdx.x & 1, threadIdx.x >> 1);
+  const double r = block_reduce<RED_OP_SUM>(acc, s_red);
+  if (threadIdx.x == 0) partials[blockIdx.x] = r;
 }
 
 // ride: leading blocks of the launch that do the packed plane (ZP_RIDE).  160- and 192-point
 // passes are held to four waves per SIMD, 128 registers instead of 135 (3 to 7% of an
-// iteration on boxes of 160 and 192 planes).
+// iteration on boxes of 160 and 192 planes); not the objective's, which would spill 25 of them
+// (192 x 512 x 512: 270 us held, 184 not).
 template <int L, int MODE, bool NTW = false, int T = ColT<L>::T, int ZP = ZPlane<L, MODE>::value>
-__global__ void __launch_bounds__(16 * T, even_plan(L, T) ? 4 : 1)
+__global__ void __launch_bounds__(16 * T, even_plan(L, T) && MODE != 3 ? 4 : 1)
     k_fft_zw(float2* __restrict__ S, int P, int ntiles, int total, int ny, long long pstride, long long bstride,
              const float2* __restrict__ tw, const float* __restrict__ ws, const float2* __restrict__ cs,
              const float* __restrict__ wnyq, const float2* __restrict__ cnyq, double* __restrict__ partials, int NT,
@@ -767,7 +799,7 @@ __global__ void __launch_bounds__(16 * T, even_plan(L, T) ? 4 : 1)
   constexpr bool PAIR = ZP == ZP_PAIR;
   if constexpr (ZP == ZP_RIDE) {
     if ((int)blockIdx.x < ride) {
-      dc_pairs<L, MODE != 4>(S, Pw, ny, pstride, tw, ws, cs, wnyq, cnyq, s_re, s_im, s_tw, NT, c, q);
+      dc_pairs<L, T, MODE != 4, false>(S, Pw, ny, pstride, tw, ws, cs, wnyq, cnyq, s_re, s_im, s_tw, NT, c, q);
       return;
     }
   }
@@ -3534,6 +3566,18 @@ static hipError_t launch_zw(float2* S, int P, int ntiles, int total, int ny, lon
                             const float2* tw, const FoldedData& fd, double* partials, int NT, bool persist,
                             hipStream_t st, int* nblocks_out, int Pw, int kxo) {
   const int cus = cu_count();
+  if constexpr (MODE == 3 && ZPlane<L, MODE>::obj_apart < (1 << 30) && ZP == ZP_PAIR) {
+    if (total > ZPlane<L, MODE>::obj_apart) {
+      int nb = 0;
+      const hipError_t e = launch_zw<L, MODE, NTW, T, ZP_APART>(S, P, ntiles, total, ny, pstride, bstride, tw, fd,
+                                                                partials, NT, persist, st, &nb, Pw, kxo);
+      if (e != hipSuccess) return e;
+      k_dc_pairs_obj<L, T><<<ny / 2 + 1, 2 * T, 0, st>>>(S, Pw, ny, pstride, tw, fd.ws, fd.cs, fd.wnyq, fd.cnyq,
+                                                        partials + nb);
+      if (nblocks_out) *nblocks_out = nb + ny / 2 + 1;
+      return hipGetLastError();
+    }
+  }
   if constexpr (ZP == ZP_RIDE) {
     if (total <= cus)
       return launch_zw<L, MODE, NTW, T, ZP_PAIR>(S, P, ntiles, total, ny, pstride, bstride, tw, fd, partials, NT,
