@@ -3522,11 +3522,9 @@ __global__ void __launch_bounds__(256) k_obj_finish(const double* __restrict__ p
 
 // ---------------------------------------------------------------- launchers
 
-// The mixed lengths, on the wide plan's threads T_ (bf16 storage).
+// The mixed lengths of a y or z axis, on the wide plan's threads T_ (bf16 storage).
 #define SPG_DISPATCH_WIDE(Lv, CALL)                                                              \
   switch (Lv) {                                                                                  \
-    case 80: { constexpr int L_ = 80, T_ = FftPlan<80>::WIDE; CALL; break; }                     \
-    case 96: { constexpr int L_ = 96, T_ = FftPlan<96>::WIDE; CALL; break; }                     \
     case 160: { constexpr int L_ = 160, T_ = FftPlan<160>::WIDE; CALL; break; }                  \
     case 192: { constexpr int L_ = 192, T_ = FftPlan<192>::WIDE; CALL; break; }                  \
     default: return hipErrorInvalidValue;                                                        \
