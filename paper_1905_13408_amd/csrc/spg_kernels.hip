@@ -709,7 +709,7 @@ __device__ __forceinline__ double dc_pairs(float2* __restrict__ S, int P, int ny
   const int ky = min(pair, ny / 2);  // past the last pair: that one again, not stored
   const int kyp = ky == 0 ? 0 : ny - ky;
   const int myky = (c & 1) ? kyp : ky;
-  const bool own = pair <= ny / 2 && ((c & 1) == 0 || ky != kyp);  // each column once
+  auto own = [&]() { return pair <= ny / 2 && ((c & 1) == 0 || ky != kyp); };  // each column once
   const int WG = P < 16 ? P : 16;
   float2* __restrict__ Sc = S + (long long)myky * P;
   float2 a[E];
@@ -745,7 +745,7 @@ __device__ __forceinline__ double dc_pairs(float2* __restrict__ S, int P, int ny
     const float2 dd = make_float2(0.5f * (z1.x - z2.x), 0.5f * (z1.y + z2.y));
     const float2 B = make_float2(dd.y, -dd.x);
     if constexpr (OBJ) {
-      if (own)
+      if (own())
         acc += 0.5 * (double)w0 * ((double)A.x * A.x + (double)A.y * A.y) - ((double)c0.x * A.x + (double)c0.y * A.y) +
                0.5 * (double)wn * ((double)B.x * B.x + (double)B.y * B.y) - ((double)cn.x * B.x + (double)cn.y * B.y);
     }
@@ -755,7 +755,7 @@ __device__ __forceinline__ double dc_pairs(float2* __restrict__ S, int P, int ny
   }
   __syncthreads();
   fft_reg<L, true, T>(a, re, im, NT, q, s_tw);
-  if (own) {
+  if (own()) {
 #pragma unroll
     for (int i = 0; i < E; ++i) Sc[(long long)(q + T * i) * pstride] = a[i];
   }
