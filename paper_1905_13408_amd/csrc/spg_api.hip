@@ -23,9 +23,10 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kStatBlocks = 1024;           // grid of the input-check / reweight kernels
-// Grid of the data check: eight blocks per CU keep twice the loads in flight on maps whose data
-// outgrow the last-level cache (512^3: 642 -> 460 us); smaller ones would only reduce twice
-// the partials.  (The fold stays at four: its stores then spread too far, 702 -> 751 us.)
+// Grid of the data check: eight blocks per CU instead of four keep twice the loads in flight
+// (512^3: 642 -> 460 us; spg_set_data 187 -> 175 us at 256^3); below 2^24 voxels a thread has too few
+// rows for that to matter and the partials to reduce are twice as many (256 x 256 x 128: 123 ->
+// 125 us, 128^3: 81 -> 88).  The fold stays at four: its stores then spread too far, 702 -> 751 us.
 int check_blocks(const Dims& d) { return d.nvox >= (1LL << 24) ? 2 * kStatBlocks : kStatBlocks; }
 constexpr int kPartials = 262144;           // fp64 partials in the workspace
 constexpr int kPartA = 0;                   // z-pass objective partials (<= 4096 blocks + 257 of the packed plane)

@@ -3810,8 +3810,8 @@ bool prox_fft_supported(const Dims& d) {
 }
 
 // 160 columns too, on the even plan's 10 threads per row, but not in bf16 storage, whose
-// rounded map buffer between the sweeps is part of its results.  Per iteration at 160^3: 86 us
-// against 95 with the separate sweeps, box 64 x 192 x 160 in fp32 47 against 58.  (192
+// rounded map buffer between the sweeps is part of its results.  Per iteration at 160^3: 79 us
+// against 88 with the separate sweeps, box 64 x 192 x 160 in fp32 46 against 53.  (192
 // columns: 141 against 120 -- six waves per block leave room for two blocks per CU only.)
 bool prox_fft_runs(const Dims& d, int store) {
   return prox_fft_supported(d) || (d.nx == 160 && d.ny % PF_TY == 0 && (store == ST_PLAIN || store == ST_COMP));
