@@ -440,8 +440,9 @@ spg_status spg_create(const spg_params* p, void* d_workspace, size_t bytes, void
   P->store = P->comp ? ST_COMP : ((p->flags & SPG_FLAG_BF16_STORAGE) ? ST_BF16 : ST_PLAIN);
   P->dn2 = dnorm2_of(p->nx, p->ny, p->nz);
   P->fused = prox_fft_runs(P->d, P->store);
-  // nominal z-slab depth of the stencil kernels: 32 planes, or fewer on small maps, whose blocks (ny / 4 tiles per slab) would otherwise be too few to keep more
-  // than a few CUs busy and each march through many planes in turn
+  // z-slab depth of the final check until a launch shape is set (the iterations': slab_depth): 32
+  // planes, or fewer on small maps, whose blocks (ny / 4 tiles per slab) would otherwise be too
+  // few to keep more than a few CUs busy and each march through many planes in turn
   while (P->zc > 4 && (long long)(p->ny / 4) * ((p->nz + P->zc - 1) / P->zc) < 512) P->zc /= 2;
   P->mon_every = (p->flags & SPG_FLAG_MONITOR) ? p->obj_every : 0;
   P->hist_iter.assign(kHistCap, 0);
